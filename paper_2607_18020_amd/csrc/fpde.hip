@@ -15,10 +15,10 @@ namespace {
 
 // Launch geometry.  A workgroup owns a TX x TY column tile (TY = 1 for 2-D
 // grids, where a "plane" is one row) and marches a chunk of planes of axis 0.
-// 3-D grids: the chunk length is chosen once per call from the backward's
-// tiling (at least kMinBwdBlocks workgroups) and shared by the forward and the
-// backward, so that the backward, which marches each chunk top down, starts on
-// the planes the forward read last (still in the memory-side infinity cache).
+// 3-D grids: the chunk length is chosen per launch (plan_chunks).  Where the
+// forward and the backward get the same one (256^3), the backward, which marches
+// each chunk top down, starts on the planes the forward read last (still in the
+// memory-side infinity cache).
 // 2-D grids: chunks sized for about kTargetBlocks2 workgroups per launch.
 // backward tile widths: a tile's x-halo columns sit in cache lines of the
 // neighbouring tiles, which L2 serves only while the two tiles march in step;
@@ -42,17 +42,11 @@ namespace {
 #ifndef FPDE_NS3_BWD_TY
 #define FPDE_NS3_BWD_TY 8
 #endif
-#ifndef FPDE_NS3_MIN_BWD_BLOCKS
-#define FPDE_NS3_MIN_BWD_BLOCKS 256
-#endif
 #ifndef FPDE_HEAT_FWD_TY
 #define FPDE_HEAT_FWD_TY 4
 #endif
 #ifndef FPDE_HEAT_BWD_TY
 #define FPDE_HEAT_BWD_TY 8
-#endif
-#ifndef FPDE_HEAT_MIN_BWD_BLOCKS
-#define FPDE_HEAT_MIN_BWD_BLOCKS 1024
 #endif
 #ifndef FPDE_TX2
 #define FPDE_TX2 256
@@ -111,9 +105,6 @@ namespace {
 #ifndef FPDE_VJP_HEAT_TY
 #define FPDE_VJP_HEAT_TY 8
 #endif
-#ifndef FPDE_VJP_TARGET3
-#define FPDE_VJP_TARGET3 512
-#endif
 #ifndef FPDE_BLOCKS2
 #define FPDE_BLOCKS2 1024
 #endif
@@ -125,25 +116,37 @@ constexpr int kTX2 = FPDE_TX2, kTX2F = FPDE_TX2_FWD, kTX2V = FPDE_TX2_VG,
               kTargetBlocks2 = FPDE_BLOCKS2;
 constexpr bool kBwdReverse = FPDE_BWD_REVERSE != 0;
 
-// 3-D grids: forward tile TXF x TYf, backward tile TXB x TYb, explicit-sensitivity
-// backward tile TXV x TYV
-template <int TXF_, int TYF, int TXB_, int TYB, int MINB, int TXV_, int TYV_, bool QF = false,
-          int RF = 4>
+// planes' worth of time that a chunk's march spends before its first step
+constexpr double kPrologue = 2.5;
+// A TX x TY tile of columns; RES workgroups of it run on a CU at once (by the
+// kernel's LDS and threads), which plan_chunks sizes a launch for.
+template <int TX_, int TY_, int RES_>
+struct Tile {
+    static constexpr int TX = TX_, TY = TY_, RES = RES_;
+};
+// 3-D grids: forward tile, backward tile, explicit-sensitivity backward tile
+template <class F, class B, class V, bool QF = false, int RF = 4>
 struct Geo3 {
     static constexpr bool D3 = true;
     static constexpr bool FWD_QUEUE = QF;  // forward: fwdq_kernel (else the LDS march)
     static constexpr int FWD_RING = RF;    // LDS march forward: slots of its plane ring
-    static constexpr int TXF = TXF_, TYf = TYF, TXB = TXB_, TYb = TYB, MIN_BWD_BLOCKS = MINB;
-    static constexpr int TXV = TXV_, TYV = TYV_;
+    // the 8-slot ring's prologue loads seven planes
+    static constexpr double FWD_PROLOGUE = RF == 8 ? 5.0 : kPrologue;
+    using TF = F;
+    using TB = B;
+    using TV = V;
 };
 // 2-D grids: one-row tiles of kTX2 nodes for every kernel
 struct Geo2 {
     static constexpr bool D3 = false;
     static constexpr bool FWD_QUEUE = true;  // (the 2-D forward is always fwdq_kernel)
 };
-// several fields with nonlinear coupling (NS)
-using GeoNS3 = Geo3<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY,
-                    FPDE_NS3_MIN_BWD_BLOCKS, FPDE_VJP_TX3, FPDE_VJP_TY3>;
+// several fields with nonlinear coupling (NS): two 512-thread forward workgroups
+// per CU (57 KB of LDS each), one 1024-thread backward (148 KB), two 256-thread
+// explicit-sensitivity ones (57 KB)
+using GeoNS3 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>,
+                    Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>,
+                    Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
 // 3D+t NS: the level march reads six time-neighbour velocities per node besides
 // the four fields, which do not fit the 128 registers of a 1024-thread backward
 // tile: 768-thread backward tiles (at 20 x 128^3, 5% faster than 512 threads)
@@ -153,17 +156,15 @@ using GeoNS3 = Geo3<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, FPDE_NS3_BWD_TX, FPDE_NS3_
 #ifndef FPDE_NS4_BWD_TY
 #define FPDE_NS4_BWD_TY 6
 #endif
-// workgroups per launch: a time level is a 3-D volume of its own, so whole-level
-// chunks leave few workgroups (and a last round of them mostly idle) on the
-// smaller volumes of space-time grids; chunks are cut for many rounds instead
-#ifndef FPDE_NS4_MIN_BLOCKS
-#define FPDE_NS4_MIN_BLOCKS 2048
-#endif
-using GeoNS4 = Geo3<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, FPDE_NS4_BWD_TX, FPDE_NS4_BWD_TY,
-                    FPDE_NS4_MIN_BLOCKS, FPDE_VJP_TX3, FPDE_VJP_TY3>;
-// one field, a Laplacian (heat, Poisson)
-using GeoHeat = Geo3<FPDE_HEAT_FWD_TX, FPDE_HEAT_FWD_TY, FPDE_HEAT_BWD_TX, FPDE_HEAT_BWD_TY,
-                     FPDE_HEAT_MIN_BWD_BLOCKS, FPDE_VJP_HEAT_TX, FPDE_VJP_HEAT_TY,
+using GeoNS4 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>,
+                    Tile<FPDE_NS4_BWD_TX, FPDE_NS4_BWD_TY, 1>,
+                    Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
+// one field, a Laplacian (heat, Poisson): 1024-thread forward and
+// explicit-sensitivity workgroups, 512-thread backward ones, bound by the 2048
+// threads of a CU
+using GeoHeat = Geo3<Tile<FPDE_HEAT_FWD_TX, FPDE_HEAT_FWD_TY, 2>,
+                     Tile<FPDE_HEAT_BWD_TX, FPDE_HEAT_BWD_TY, 4>,
+                     Tile<FPDE_VJP_HEAT_TX, FPDE_VJP_HEAT_TY, 2>,
                      FPDE_HEAT_FWD_QUEUE != 0, FPDE_HEAT_FWD_RING>;
 
 template <class OP_, class GEO_>
@@ -344,21 +345,58 @@ Dims tile_dims(const Dims& n, int TX, int TY, int zc) {
     return dm;
 }
 
-// Chunk length giving a launch with TX x TY tiles about `target` workgroups
-// (each chunk at least one plane; 3D+t grids: over all launched levels, and at
-// least kMinChunkT planes, as a chunk of a few planes re-reads its halo planes
-// and its march prologue for little work).
-constexpr int kMinChunkT = 8;
-int chunk_planes(const Dims& n, int TX, int TY, int target) {
+// Chunk length of a 3-D march with TX x TY tiles of which RES workgroups fit a
+// CU at once.  A launch runs in rounds of CUs * RES workgroups, each as long as
+// one chunk's march (its planes plus about kPrologue planes' worth of prologue:
+// the first planes' latency and the halo planes' residuals), so a launch a little over a whole
+// number of rounds idles most of the chip in its last one: at 150 x 131 x 257 the
+// NS-3D backward takes 93 us cut into 306 workgroups and 61 us cut into 255, and
+// the 2D+t one at 33 x 201 x 259 28 us in 312 and 20 us in 234.  The rule takes,
+// among the chunk counts that just fill 1, 2, ... CUs' worth of workgroups, the
+// one with the shortest estimated march.  In a last round with k of RES
+// workgroups per CU a step costs 0.3 + 0.7 k / RES of a full round's (128^3,
+// two per CU: 0.67 at one).  A loss adds one atomic per workgroup of the last
+// round, serialised at 12 ns, about 0.015 of a step (`loss`).
+#ifndef FPDE_CUS
+#define FPDE_CUS 256
+#endif
+constexpr int kCUs = FPDE_CUS;
+struct Chunks {
+    int zc;       // planes per chunk
+    double cost;  // estimated time, in steps of a full round
+};
+Chunks plan_chunks(const Dims& n, int TX, int TY, int res, bool loss, double prologue = kPrologue) {
     const long long tiles =
         (long long)((n.nx + TX - 1) / TX) * ((n.ny + TY - 1) / TY) * n.nlev;
     const int nplanes = n.nz - 2 * n.zlo;
+    Chunks best = {nplanes, 0.0};
+    long long tried = 0;
+    // CU loads 1 .. res (one round, in part), then whole rounds up to 8
+    for (int j = 1; j <= res + 7; ++j) {
+        const long long load = j <= res ? j : (long long)(j - res + 1) * res;
+        long long nch = load * kCUs / tiles;
+        nch = nch < 1 ? 1 : nch > nplanes ? nplanes : nch;
+        if (nch == tried) continue;
+        tried = nch;
+        const int zc = (int)((nplanes + nch - 1) / nch);
+        const long long W = tiles * ((nplanes + zc - 1) / zc);
+        const long long slots = (long long)kCUs * res, full = W / slots;
+        const long long k = (W - full * slots + kCUs - 1) / kCUs;
+        double cost = (zc + prologue) * ((double)full + (k ? 0.3 + 0.7 * (double)k / res : 0.0));
+        if (loss) cost += 0.015 * (double)(W < slots ? W : slots);
+        if (j == 1 || cost < best.cost) best = {zc, cost};
+    }
+    return best;
+}
+
+// 2-D grids: chunk length giving about `target` workgroups (a chunk holds at
+// least one row)
+int chunk_rows(const Dims& n, int TX, int target) {
+    const long long tiles = (n.nx + TX - 1) / TX;
+    const int nrows = n.nz - 2 * n.zlo;
     long long nch = (target + tiles - 1) / tiles;
-    if (n.nt > 1 && nch > (nplanes + kMinChunkT - 1) / kMinChunkT)
-        nch = (nplanes + kMinChunkT - 1) / kMinChunkT;
-    if (nch < 1) nch = 1;
-    if (nch > nplanes) nch = nplanes;
-    return (int)((nplanes + nch - 1) / nch);
+    if (nch > nrows) nch = nrows;
+    return (int)((nrows + nch - 1) / nch);
 }
 
 int check_outputs(const Req& r, const fpde_grid4*, const float* const* fields,
@@ -477,12 +515,24 @@ int launch_bwdq(const Req& r, const double* dloss, int zc) {
     return st;
 }
 
-// 3-D: the chunk length shared by the forward and the backward
-template <class GEO>
-int zc3(const Req& r) {
-    return chunk_planes(r.dims, GEO::TXB, GEO::TYb, GEO::MIN_BWD_BLOCKS);
+int zc2(const Req& r) { return chunk_rows(r.dims, kTX2, kTargetBlocks2); }
+
+// 3-D launches: tile and chunk length
+template <class GEO, class OP>
+int launch_fwd3(const Req& r, bool store, double* loss) {
+    using T = typename GEO::TF;
+    const int zc = plan_chunks(r.dims, T::TX, T::TY, T::RES, true, GEO::FWD_PROLOGUE).zc;
+    if constexpr (GEO::FWD_QUEUE)
+        return launch_fwdq<OP, T::TX, T::TY>(r, store, loss, zc);
+    else
+        return launch_fwd<OP, T::TX, T::TY, GEO::FWD_RING>(r, store, loss, zc);
 }
-int zc2(const Req& r) { return chunk_planes(r.dims, kTX2, 1, kTargetBlocks2); }
+template <class GEO, class OP>
+int launch_bwd3(const Req& r, const double* dloss, double* loss) {
+    using T = typename GEO::TB;
+    const int zc = plan_chunks(r.dims, T::TX, T::TY, T::RES, loss != nullptr).zc;
+    return launch_bwd<OP, T::TX, T::TY>(r, dloss, zc, loss);
+}
 
 template <class OP>
 int launch_bc(const Req& r, const double* dloss) {
@@ -517,10 +567,8 @@ int launch_tm(const Req& r, const double* dloss) {
 // Explicit-sensitivity backward: every plane of axis 0 is marched (zlo = 0),
 // on a 3D+t grid in every time level.
 template <class OP, int TX, int TY>
-int launch_vjp(const Req& r, bool acc, int target) {
-    Dims base = levels(r.dims, true);
-    base.zlo = 0;
-    const Dims dm = tile_dims(base, TX, TY, chunk_planes(base, TX, TY, target));
+int launch_vjp(const Req& r, bool acc, const Dims& base, int zc) {
+    const Dims dm = tile_dims(base, TX, TY, zc);
     int st = FPDE_OK;
     with_flag(acc, [&](auto ac) {
         with_flag(dm.per, [&](auto per) {
@@ -532,14 +580,18 @@ int launch_vjp(const Req& r, bool acc, int target) {
 }
 
 int run_vjp(const Req& r, bool acc) {
+    Dims base = levels(r.dims, true);
+    base.zlo = 0;
     return with_op(r.op, [&](auto tag) {
         using OP = typename decltype(tag)::OP;
         using GEO = typename decltype(tag)::GEO;
-        if constexpr (GEO::D3)
-            return launch_vjp<OP, GEO::TXV, GEO::TYV>(
-                r, acc, OP::TIME ? GEO::MIN_BWD_BLOCKS : FPDE_VJP_TARGET3);
-        else
-            return launch_vjp<OP, kTX2, 1>(r, acc, kTargetBlocks2);
+        if constexpr (GEO::D3) {
+            using T = typename GEO::TV;
+            const int zc = plan_chunks(base, T::TX, T::TY, T::RES, false).zc;
+            return launch_vjp<OP, T::TX, T::TY>(r, acc, base, zc);
+        } else {
+            return launch_vjp<OP, kTX2, 1>(r, acc, base, chunk_rows(base, kTX2, kTargetBlocks2));
+        }
     });
 }
 
@@ -549,10 +601,8 @@ int run_fwd(const Req& r0, bool store, double* loss) {
     return with_op(r.op, [&](auto tag) {
         using OP = typename decltype(tag)::OP;
         using GEO = typename decltype(tag)::GEO;
-        if constexpr (GEO::D3 && GEO::FWD_QUEUE)
-            return launch_fwdq<OP, GEO::TXF, GEO::TYf>(r, store, loss, zc3<GEO>(r));
-        else if constexpr (GEO::D3)
-            return launch_fwd<OP, GEO::TXF, GEO::TYf, GEO::FWD_RING>(r, store, loss, zc3<GEO>(r));
+        if constexpr (GEO::D3)
+            return launch_fwd3<GEO, OP>(r, store, loss);
         else
             return launch_fwdq<OP, kTX2F, 1>(r, store, loss, zc2(r));
     });
@@ -574,12 +624,12 @@ int run_bwd(const Req& r0, const double* dloss, double* loss = nullptr) {
         using OP = typename decltype(tag)::OP;
         using GEO = typename decltype(tag)::GEO;
         if constexpr (OP::TIME) {
-            int st = launch_bwd<OP, GEO::TXB, GEO::TYb>(r, dloss, zc3<GEO>(r), loss);
+            int st = launch_bwd3<GEO, OP>(r, dloss, loss);
             if (st == FPDE_OK) st = launch_tm<OP>(r, dloss);
             if (st == FPDE_OK && loss && !r.dims.per) st = launch_bc<OP>(r, dloss);
             return st;
         } else if constexpr (GEO::D3)
-            return launch_bwd<OP, GEO::TXB, GEO::TYb>(r, dloss, zc3<GEO>(r), loss);
+            return launch_bwd3<GEO, OP>(r, dloss, loss);
         else if (loss)
             return launch_bwd<OP, kTX2V, 1>(r, dloss, zc2(r), loss);
         else if (FPDE_BWD2_QUEUE)

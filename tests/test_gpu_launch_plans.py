@@ -1,0 +1,56 @@
+"""3-D launches at the sizes where the launch rule changes its mind: a chunk
+count that just fills or just misses a round of workgroups, one-plane chunks, a
+last chunk of one plane, a single chunk, and more tiles than a round holds.
+Every entry point against the oracle, node by node, in both boundary modes."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from paper_2607_18020_amd import workloads as W
+from tests import gpu_helpers as H
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    (W.NS_3D_BE, (3, 40, 130)),      # one interior plane
+    (W.NS_3D_BE, (67, 64, 66)),      # one- and two-plane chunks, two tiles per row
+    (W.NS_3D_STEADY, (62, 9, 129)),  # one plane per chunk, a last tile of one column
+    (W.NS_2DT, (5, 290, 520)),       # more tiles than a round of the backward holds
+    (W.HEAT_3D_BE, (37, 33, 65)),
+    (W.POISSON_3D, (70, 12, 257)),
+    (W.NS_3DT, (4, 19, 13, 131)),
+]
+
+
+@pytest.mark.parametrize("bc_mode", [0, 1])
+@pytest.mark.parametrize("op,shape", CASES,
+                         ids=[f"{W.OP_NAMES[o]}-{'x'.join(map(str, s))}" for o, s in CASES])
+def test_launch_plans(op, shape, bc_mode, oracle_mod):
+    import torch  # noqa: PLC0415
+    from paper_2607_18020_amd import binding as B  # noqa: PLC0415
+    wl = W.normal_fields(op, shape, 45)
+    print(f"case launch plan {W.OP_NAMES[op]} {shape} bc_mode={bc_mode}", flush=True)
+    a = (op, shape, wl.h, wl.coeffs, wl.fields)
+    R_ref = oracle_mod.residual(*a, wl.consts, bc_mode=bc_mode)
+    L_ref = oracle_mod.loss(*a, wl.consts, bc_mode=bc_mode)
+    g_ref = oracle_mod.grad(*a, wl.consts, bc_mode=bc_mode)
+    R, L, g = H.run_gpu(wl, bc_mode=bc_mode)
+    for r, ref in zip(R, R_ref):
+        inner = (lambda x: x) if bc_mode else H.interior
+        assert H.max_rel_err(inner(r), inner(ref)) <= H.TOL_RES
+    assert abs(L - L_ref) <= H.TOL_RES * abs(L_ref)
+    for x, ref in zip(g, g_ref):
+        assert np.isfinite(x).all() and H.max_rel_err(x, ref) <= H.TOL_GRAD
+    f = [torch.from_numpy(x).cuda() for x in wl.fields]
+    c = [torch.from_numpy(x).cuda() for x in wl.consts]
+    Lv, gv = B.fpde_residual_value_and_grad(op, f, c, wl.h, wl.coeffs, bc_mode=bc_mode)
+    assert abs(Lv.item() - L_ref) <= H.TOL_RES * abs(L_ref)
+    sens = W.sensitivities(op, shape, 8)
+    gj = B.fpde_residual_vjp(op, f, wl.h, wl.coeffs, [torch.from_numpy(s).cuda() for s in sens],
+                             bc_mode=bc_mode)
+    gj_ref = oracle_mod.vjp(*a, wl.consts, sens, bc_mode=bc_mode)
+    for x, ref in zip(gv, g_ref):
+        assert H.max_rel_err(x.cpu().numpy(), ref) <= H.TOL_GRAD
+    for x, ref in zip(gj, gj_ref):
+        assert H.max_rel_err(x.cpu().numpy(), ref) <= H.TOL_GRAD
