@@ -119,13 +119,18 @@ constexpr bool kBwdReverse = FPDE_BWD_REVERSE != 0;
 // planes' worth of time that a chunk's march spends before its first step
 constexpr double kPrologue = 2.5;
 // A TX x TY tile of columns; RES workgroups of it run on a CU at once (by the
-// kernel's LDS and threads), which plan_chunks sizes a launch for.
-template <int TX_, int TY_, int RES_>
+// kernel's LDS and threads), which plan_chunks sizes a launch for, and a step of
+// a full round takes STEP percent of the wide tile's.
+template <int TX_, int TY_, int RES_, int STEP_ = 100>
 struct Tile {
-    static constexpr int TX = TX_, TY = TY_, RES = RES_;
+    static constexpr int TX = TX_, TY = TY_, RES = RES_, STEP = STEP_;
 };
-// 3-D grids: forward tile, backward tile, explicit-sensitivity backward tile
-template <class F, class B, class V, bool QF = false, int RF = 4>
+// 3-D grids: forward, backward and explicit-sensitivity backward tiles, each a
+// wide one (fewer cache lines shared across tile edges: the faster on wide rows)
+// and a narrow one, which leaves fewer lanes idle where the last axis is not a
+// multiple of the wide tile, and whose smaller workgroups have the shorter step
+// on a grid that does not fill the chip; with_tile picks.
+template <class F, class F2, class B, class B2, class V, class V2, bool QF = false, int RF = 4>
 struct Geo3 {
     static constexpr bool D3 = true;
     static constexpr bool FWD_QUEUE = QF;  // forward: fwdq_kernel (else the LDS march)
@@ -133,8 +138,11 @@ struct Geo3 {
     // the 8-slot ring's prologue loads seven planes
     static constexpr double FWD_PROLOGUE = RF == 8 ? 5.0 : kPrologue;
     using TF = F;
+    using TF2 = F2;
     using TB = B;
+    using TB2 = B2;
     using TV = V;
+    using TV2 = V2;
 };
 // 2-D grids: one-row tiles of kTX2 nodes for every kernel
 struct Geo2 {
@@ -142,29 +150,38 @@ struct Geo2 {
     static constexpr bool FWD_QUEUE = true;  // (the 2-D forward is always fwdq_kernel)
 };
 // several fields with nonlinear coupling (NS): two 512-thread forward workgroups
-// per CU (57 KB of LDS each), one 1024-thread backward (148 KB), two 256-thread
-// explicit-sensitivity ones (57 KB)
-using GeoNS3 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>,
-                    Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>,
-                    Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
+// per CU (57 KB of LDS each), one 1024-thread backward (148 KB) or two 512-thread
+// ones (79 KB), two 256-thread explicit-sensitivity ones (57 KB).  The narrow
+// tiles' steps, measured on grids of many full rounds: forward 87 -> 91 us at
+// 256^3 and 28.1 -> 28.6 at 245 x 233 x 127; backward 154 -> 173 and 58.6 ->
+// 60.4.  Where they win: NS-3D backward 150 x 131 x 257 61 -> 54 us (5 tiles of 64
+// across a row instead of 3 of 128), 64^3 10.8 -> 8.1, 28 x 39 x 47 9.0 -> 7.0;
+// forward 64^3 10.4 -> 8.6 (5.5 of it the loss fill and the launches).
+using GeoNS3 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>, Tile<64, 8, 2, 104>,
+                    Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>, Tile<64, 8, 2, 106>,
+                    Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>, Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
 // 3D+t NS: the level march reads six time-neighbour velocities per node besides
 // the four fields, which do not fit the 128 registers of a 1024-thread backward
-// tile: 768-thread backward tiles (at 20 x 128^3, 5% faster than 512 threads)
+// tile: 768-thread wide backward tiles (at 20 x 128^3, 5% faster than 512
+// threads), 512-thread narrow ones, one to a CU
 #ifndef FPDE_NS4_BWD_TX
 #define FPDE_NS4_BWD_TX 128
 #endif
 #ifndef FPDE_NS4_BWD_TY
 #define FPDE_NS4_BWD_TY 6
 #endif
-using GeoNS4 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>,
-                    Tile<FPDE_NS4_BWD_TX, FPDE_NS4_BWD_TY, 1>,
-                    Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
-// one field, a Laplacian (heat, Poisson): 1024-thread forward and
-// explicit-sensitivity workgroups, 512-thread backward ones, bound by the 2048
-// threads of a CU
-using GeoHeat = Geo3<Tile<FPDE_HEAT_FWD_TX, FPDE_HEAT_FWD_TY, 2>,
+using GeoNS4 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>, Tile<64, 8, 2, 104>,
+                    Tile<FPDE_NS4_BWD_TX, FPDE_NS4_BWD_TY, 1>, Tile<64, 8, 1, 75>,
+                    Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>, Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
+// one field, a Laplacian (heat, Poisson): 1024-thread wide forward and
+// explicit-sensitivity workgroups, the others 512 threads, bound by the 2048
+// threads of a CU.  The narrow forward: 28.6 -> 29.6 us at 256^3, 11.8 -> 8.4 at
+// 97 x 90 x 41 and 9.1 -> 6.9 at 44 x 56 x 32; explicit sensitivities 26.1 -> 26.8,
+// 6.0 -> 4.8 and 4.6 -> 3.8.  (The backward's wide tile is a 64-node one.)
+using GeoHeat = Geo3<Tile<FPDE_HEAT_FWD_TX, FPDE_HEAT_FWD_TY, 2>, Tile<64, 8, 4, 103>,
                      Tile<FPDE_HEAT_BWD_TX, FPDE_HEAT_BWD_TY, 4>,
-                     Tile<FPDE_VJP_HEAT_TX, FPDE_VJP_HEAT_TY, 2>,
+                     Tile<FPDE_HEAT_BWD_TX, FPDE_HEAT_BWD_TY, 4>,
+                     Tile<FPDE_VJP_HEAT_TX, FPDE_VJP_HEAT_TY, 2>, Tile<64, 8, 4, 103>,
                      FPDE_HEAT_FWD_QUEUE != 0, FPDE_HEAT_FWD_RING>;
 
 template <class OP_, class GEO_>
@@ -517,21 +534,41 @@ int launch_bwdq(const Req& r, const double* dloss, int zc) {
 
 int zc2(const Req& r) { return chunk_rows(r.dims, kTX2, kTargetBlocks2); }
 
-// 3-D launches: tile and chunk length
+// f(Tile<...>{}, zc) for the wide tile A or (if narrow) the narrow tile B of a
+// 3-D launch, whichever has the shorter estimated march (plan_chunks)
+template <class A, class B, class F>
+int with_tile(const Dims& n, bool loss, double prologue, bool narrow, F&& f) {
+    const Chunks a = plan_chunks(n, A::TX, A::TY, A::RES, loss, prologue);
+    if (!std::is_same<A, B>::value && narrow) {
+        const Chunks b = plan_chunks(n, B::TX, B::TY, B::RES, loss, prologue);
+        if (b.cost * B::STEP < a.cost * A::STEP) return f(B{}, b.zc);
+    }
+    return f(A{}, a.zc);
+}
+
+// Residual stores beyond the 32 MB of the L2s keep the wide tile: rows of a
+// ragged grid are not aligned to cache lines, and each tile edge splits one
+// between two workgroups' non-temporal stores (NS-3D 150 x 131 x 257, forward
+// with residuals: 47 us with 128-wide tiles, 58 with 64-wide ones).
 template <class GEO, class OP>
 int launch_fwd3(const Req& r, bool store, double* loss) {
-    using T = typename GEO::TF;
-    const int zc = plan_chunks(r.dims, T::TX, T::TY, T::RES, true, GEO::FWD_PROLOGUE).zc;
-    if constexpr (GEO::FWD_QUEUE)
-        return launch_fwdq<OP, T::TX, T::TY>(r, store, loss, zc);
-    else
-        return launch_fwd<OP, T::TX, T::TY, GEO::FWD_RING>(r, store, loss, zc);
+    const bool narrow = !store || r.N * OP::NR * 4 <= (32LL << 20);
+    return with_tile<typename GEO::TF, typename GEO::TF2>(
+        r.dims, true, GEO::FWD_PROLOGUE, narrow, [&](auto t, int zc) {
+            using T = decltype(t);
+            if constexpr (GEO::FWD_QUEUE)
+                return launch_fwdq<OP, T::TX, T::TY>(r, store, loss, zc);
+            else
+                return launch_fwd<OP, T::TX, T::TY, GEO::FWD_RING>(r, store, loss, zc);
+        });
 }
 template <class GEO, class OP>
 int launch_bwd3(const Req& r, const double* dloss, double* loss) {
-    using T = typename GEO::TB;
-    const int zc = plan_chunks(r.dims, T::TX, T::TY, T::RES, loss != nullptr).zc;
-    return launch_bwd<OP, T::TX, T::TY>(r, dloss, zc, loss);
+    return with_tile<typename GEO::TB, typename GEO::TB2>(
+        r.dims, loss != nullptr, kPrologue, true, [&](auto t, int zc) {
+            using T = decltype(t);
+            return launch_bwd<OP, T::TX, T::TY>(r, dloss, zc, loss);
+        });
 }
 
 template <class OP>
@@ -586,9 +623,11 @@ int run_vjp(const Req& r, bool acc) {
         using OP = typename decltype(tag)::OP;
         using GEO = typename decltype(tag)::GEO;
         if constexpr (GEO::D3) {
-            using T = typename GEO::TV;
-            const int zc = plan_chunks(base, T::TX, T::TY, T::RES, false).zc;
-            return launch_vjp<OP, T::TX, T::TY>(r, acc, base, zc);
+            return with_tile<typename GEO::TV, typename GEO::TV2>(
+                base, false, kPrologue, true, [&](auto t, int zc) {
+                    using T = decltype(t);
+                    return launch_vjp<OP, T::TX, T::TY>(r, acc, base, zc);
+                });
         } else {
             return launch_vjp<OP, kTX2, 1>(r, acc, base, chunk_rows(base, kTX2, kTargetBlocks2));
         }

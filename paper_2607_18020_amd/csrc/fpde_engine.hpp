@@ -743,8 +743,13 @@ __global__ __launch_bounds__(TX* TY) void fwdq_kernel(Ptrs P, Dims D, KCoef K, d
 // the equations, float64 accumulation, one float64 atomic per workgroup onto
 // *loss, which the host zeroes first): the fields are read once for both.
 
+// Waves per SIMD asked for: 512-thread tiles of several fields run two to a CU
+// (their LDS allows it), which needs four waves of at most 128 VGPRs per SIMD.
+template <class OP, int NT>
+constexpr int kBwdMinW = (OP::NF > 1 && OP::DIM == 3 && !OP::TIME && NT == 512) ? 4 : FPDE_BWD_MINW;
+
 template <class OP, int TX, int TY, bool REV, bool LOSS, bool PER>
-__global__ __launch_bounds__(TX* TY, FPDE_BWD_MINW) void bwd_kernel(Ptrs P, Dims D, KCoef K,
+__global__ __launch_bounds__(TX* TY, (kBwdMinW<OP, TX * TY>)) void bwd_kernel(Ptrs P, Dims D, KCoef K,
                                                                     const double* dloss,
                                                                     double two_over_M,
                                                                     double inv_M, double* loss) {

@@ -1,6 +1,7 @@
 """3-D launches at the sizes where the launch rule changes its mind: a chunk
 count that just fills or just misses a round of workgroups, one-plane chunks, a
-last chunk of one plane, a single chunk, and more tiles than a round holds.
+last chunk of one plane, a single chunk, more tiles than a round holds, and the
+wide and narrow tiles of each kernel (ragged against both).
 Every entry point against the oracle, node by node, in both boundary modes."""
 from __future__ import annotations
 
@@ -17,9 +18,12 @@ CASES = [
     (W.NS_3D_BE, (67, 64, 66)),      # one- and two-plane chunks, two tiles per row
     (W.NS_3D_STEADY, (62, 9, 129)),  # one plane per chunk, a last tile of one column
     (W.NS_2DT, (5, 290, 520)),       # more tiles than a round of the backward holds
-    (W.HEAT_3D_BE, (37, 33, 65)),
+    (W.NS_3D_BE, (17, 33, 193)),     # narrow backward tiles, a last one of one column
+    (W.HEAT_3D_BE, (37, 33, 65)),    # narrow forward and explicit-sensitivity tiles
+    (W.HEAT_3D_BE, (20, 41, 255)),   # wide ones
     (W.POISSON_3D, (70, 12, 257)),
     (W.NS_3DT, (4, 19, 13, 131)),
+    (W.NS_3DT, (5, 9, 21, 33)),
 ]
 
 
