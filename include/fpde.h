@@ -270,6 +270,28 @@ int fpde_residual_vjp4(int op, const fpde_grid4* grid, const fpde_coeffs* coeffs
                        const float* const* fields, const float* const* sens, int accumulate,
                        float* const* grads, void* stream);
 
+/* fpde_residual_fwd4 and fpde_residual_value_and_grad4 with a workspace for the
+ * loss: the workgroups' sums meet there instead of in one float64 atomic each on
+ * *loss, which needs no fill kernel before the launch (one launch less) and adds
+ * them in a fixed order.
+ *   workspace  FPDE_WORKSPACE_BYTES of device memory, 8-byte aligned, owned by the
+ *              caller; must not overlap any other argument array (FPDE_ERR_ARG).
+ *              Zeroed by the caller once, before its first use; every call leaves
+ *              it ready for the next one on the same stream.  Calls that may run at the same time
+ *              (on different streams) need a workspace each.
+ * Launches of more than 4096 workgroups, and calls on a stream that is being
+ * captured, leave the workspace alone and queue what the calls above queue (so a
+ * captured graph holds no reference to it).  Everything else as the calls above. */
+#define FPDE_WORKSPACE_BYTES 65536
+int fpde_residual_fwd_ws4(int op, const fpde_grid4* grid, const fpde_coeffs* coeffs,
+                          const float* const* fields, const float* const* consts,
+                          float* const* residual_out, double* loss, void* workspace,
+                          void* stream);
+int fpde_residual_value_and_grad_ws4(int op, const fpde_grid4* grid, const fpde_coeffs* coeffs,
+                                     const float* const* fields, const float* const* consts,
+                                     const double* dloss, double* loss, float* const* grads,
+                                     void* workspace, void* stream);
+
 /* Static string naming a status code (never NULL). */
 const char* fpde_status_string(int status);
 

@@ -27,7 +27,10 @@ STATUS_NAMES = {0: "FPDE_OK", -1: "FPDE_ERR_ARG", -2: "FPDE_ERR_SHAPE", -3: "FPD
 # the compute entry points; each also exists with a 4 suffix taking fpde_grid4
 CALLS = ("fpde_residual_fwd", "fpde_residual_bwd", "fpde_bc_correct", "fpde_residual_vjp",
          "fpde_residual_value_and_grad")
-EXPORTED = ("fpde_op_info",) + CALLS + tuple(c + "4" for c in CALLS) + \
+# the loss calls with a workspace for the workgroups' sums (fpde_grid4 only)
+WS_CALLS = ("fpde_residual_fwd_ws4", "fpde_residual_value_and_grad_ws4")
+WORKSPACE_BYTES = 65536
+EXPORTED = ("fpde_op_info",) + CALLS + tuple(c + "4" for c in CALLS) + WS_CALLS + \
     ("fpde_status_string", "fpde_version")
 
 
@@ -78,6 +81,10 @@ def _load():
                 fn = getattr(lib, name + sfx)
                 fn.argtypes = args
                 fn.restype = ctypes.c_int
+        for name in WS_CALLS:  # (the 4-suffixed call's arguments, the workspace before the stream)
+            fn = getattr(lib, name)
+            fn.argtypes = sig[name[:-4]][:-1] + [vp, vp]
+            fn.restype = ctypes.c_int
         lib.fpde_status_string.argtypes = [ctypes.c_int]
         lib.fpde_status_string.restype = ctypes.c_char_p
         lib.fpde_version.argtypes = []
@@ -113,9 +120,9 @@ def op_info(op: int):
     return tuple(x.value for x in v)  # ndim, n_fields, n_consts, n_residuals
 
 
-def make_grid(shape: Sequence[int], h: Sequence[float], bc_mode: int = 0):
-    """fpde_grid for up to three axes, fpde_grid4 for four."""
-    g = FpdeGrid4() if len(shape) == 4 else FpdeGrid()
+def make_grid(shape: Sequence[int], h: Sequence[float], bc_mode: int = 0, four: bool = False):
+    """fpde_grid for up to three axes, fpde_grid4 for four (or if ``four``)."""
+    g = FpdeGrid4() if four or len(shape) == 4 else FpdeGrid()
     g.ndim = len(shape)
     g.bc_mode = int(bc_mode)
     for a, (n, hh) in enumerate(zip(shape, h)):
@@ -168,6 +175,12 @@ def _used_on(stream, *tensors):
     if stream is not None and stream != torch.cuda.current_stream():
         for t in tensors:
             t.record_stream(stream)
+
+
+def _loss_workspace(stream, dev) -> torch.Tensor:
+    """A zeroed loss workspace, allocated and zeroed on the stream whose calls use it."""
+    with torch.cuda.stream(stream):  # (None: the current stream)
+        return torch.zeros(WORKSPACE_BYTES // 8, dtype=torch.float64, device=dev)
 
 
 def fpde_residual_fwd(op: int, fields, consts, h, coeffs, *, residual_out=None,
@@ -305,28 +318,31 @@ def bind(entry: str, op: int, fields, consts, h, coeffs, *, dloss=None, grads=No
     dev = fields[0].device
     consts = list(consts) if consts is not None else []
     _check_tensors(list(fields) + consts, shape, f"bind {entry}")
-    g, c = make_grid(shape, h, bc_mode), make_coeffs(coeffs)
+    with_loss = entry in ("fwd", "value_and_grad")
+    g, c = make_grid(shape, h, bc_mode, four=with_loss), make_coeffs(coeffs)
     fa = _ptr_array(fields)
     ca = _ptr_array(consts) if len(consts) else None
     sh = _stream(stream)
     lib = _load()
     keep = [g, c, fa, ca, list(fields), consts]
-    if entry in ("fwd", "value_and_grad"):
+    if with_loss:
         if loss is None:
             loss = torch.empty((), dtype=torch.float64, device=dev)
             _used_on(stream, loss)
         if loss.dtype != torch.float64 or loss.device != dev or loss.numel() != 1:
             raise ValueError(f"bind {entry}: loss must be a one-element float64 tensor on the "
                              "fields' device")
-        keep.append(loss)
+        ws = _loss_workspace(stream, dev)
+        keep += [loss, ws]
     if entry == "fwd":
         ra = None
         if residual_out is not None:
             _check_tensors(residual_out, shape, "bind fwd residual_out")
             ra = _ptr_array(residual_out)
             keep += [ra, list(residual_out)]
-        args = (int(op), ctypes.byref(g), ctypes.byref(c), fa, ca, ra, loss.data_ptr(), sh)
-        return BoundCall("fpde_residual_fwd", _entry("fpde_residual_fwd", shape), args, keep, loss)
+        args = (int(op), ctypes.byref(g), ctypes.byref(c), fa, ca, ra, loss.data_ptr(),
+                ws.data_ptr(), sh)
+        return BoundCall("fpde_residual_fwd", lib.fpde_residual_fwd_ws4, args, keep, loss)
     if grads is None:
         grads = [torch.empty_like(f) for f in fields]
         _used_on(stream, *grads)
@@ -349,9 +365,9 @@ def bind(entry: str, op: int, fields, consts, h, coeffs, *, dloss=None, grads=No
     keep.append(dloss)
     if entry == "value_and_grad":
         args = (int(op), ctypes.byref(g), ctypes.byref(c), fa, ca, dloss.data_ptr(),
-                loss.data_ptr(), ga, sh)
-        return BoundCall("fpde_residual_value_and_grad",
-                         _entry("fpde_residual_value_and_grad", shape), args, keep, (loss, grads))
+                loss.data_ptr(), ga, ws.data_ptr(), sh)
+        return BoundCall("fpde_residual_value_and_grad", lib.fpde_residual_value_and_grad_ws4,
+                         args, keep, (loss, grads))
     if entry not in ("bwd", "bc"):
         raise ValueError(f"bind: unknown entry point {entry!r}")
     name = "fpde_residual_bwd" if entry == "bwd" else "fpde_bc_correct"

@@ -237,6 +237,7 @@ struct Req {
     long long N, M;
     Ptrs P;
     hipStream_t stream;
+    double* ws;  // loss workspace of the call, or nullptr
 };
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
@@ -308,6 +309,7 @@ int validate_common(int op, const fpde_grid4* g, const fpde_coeffs* c, const flo
     for (int j = 0; j < nc; ++j)
         if ((uintptr_t)consts[j] & 3u) return FPDE_ERR_ALIGN;
 
+    r->ws = nullptr;
     r->op = op;
     r->K = K;
     r->N = N;
@@ -372,8 +374,8 @@ Dims tile_dims(const Dims& n, int TX, int TY, int zc) {
 // among the chunk counts that just fill 1, 2, ... CUs' worth of workgroups, the
 // one with the shortest estimated march.  In a last round with k of RES
 // workgroups per CU a step costs 0.3 + 0.7 k / RES of a full round's (128^3,
-// two per CU: 0.67 at one).  A loss adds one atomic per workgroup of the last
-// round, serialised at 12 ns, about 0.015 of a step (`loss`).
+// two per CU: 0.67 at one).  A loss without a workspace adds one atomic per
+// workgroup of the last round, serialised at 12 ns, about 0.015 of a step (`loss`).
 #ifndef FPDE_CUS
 #define FPDE_CUS 256
 #endif
@@ -453,8 +455,12 @@ int launch(void (*k)(P...), dim3 grid, dim3 block, hipStream_t s,
                : FPDE_ERR_HIP;
 }
 
-int zero_loss(const Req& r, double* loss) {
-    return launch(fill_f64_kernel, dim3(1), dim3(1), r.stream, loss, 0.0);
+// Before a launch of nblocks workgroups that sums a loss: the workspace it goes
+// through, if the call has one large enough for the launch (a longer launch hides its
+// atomics, which are spread over its rounds), else *loss zeroed
+int begin_loss(const Req& r, int nblocks, double* loss, double** ws) {
+    *ws = r.ws && nblocks <= kWsMaxBlocks ? r.ws : nullptr;
+    return *ws ? FPDE_OK : launch(fill_f64_kernel, dim3(1), dim3(1), r.stream, loss, 0.0);
 }
 
 // ---- launches, per op type
@@ -470,7 +476,8 @@ void with_flag(bool v, F&& f) {
 template <class OP, int TX, int TY, int RD>
 int launch_fwd(const Req& r, bool store, double* loss, int zc) {
     const Dims dm = tile_dims(r.dims, TX, TY, zc);
-    int st = zero_loss(r, loss);
+    double* ws;
+    int st = begin_loss(r, dm.nblocks, loss, &ws);
     if (st != FPDE_OK) return st;
     if (OP::TIME && store && !dm.per) {  // the end time levels hold no residual node
         st = launch(zero_levels_kernel<OP::NR>, dim3((unsigned)((2 * dm.vol + 255) / 256)),
@@ -480,7 +487,8 @@ int launch_fwd(const Req& r, bool store, double* loss, int zc) {
     with_flag(store, [&](auto sr) {
         with_flag(dm.per, [&](auto per) {
             st = launch(fwd_kernel<OP, TX, TY, decltype(sr)::value, decltype(per)::value, RD>,
-                        dim3(dm.nblocks), dim3(TX * TY), r.stream, r.P, dm, r.K, r.inv_M, loss);
+                        dim3(dm.nblocks), dim3(TX * TY), r.stream, r.P, dm, r.K, r.inv_M, loss,
+                        ws);
         });
     });
     return st;
@@ -490,13 +498,15 @@ int launch_fwd(const Req& r, bool store, double* loss, int zc) {
 template <class OP, int TX, int TY>
 int launch_fwdq(const Req& r, bool store, double* loss, int zc) {
     const Dims dm = tile_dims(r.dims, TX, TY, zc);
-    int st = zero_loss(r, loss);
+    double* ws;
+    int st = begin_loss(r, dm.nblocks, loss, &ws);
     if (st != FPDE_OK) return st;
     with_flag(store, [&](auto sr) {
         with_flag(dm.per, [&](auto per) {
             st = launch(fwdq_kernel<OP, TX, TY, FPDE_FWD2_Q, decltype(sr)::value,
                                     decltype(per)::value>,
-                        dim3(dm.nblocks), dim3(TX * TY), r.stream, r.P, dm, r.K, r.inv_M, loss);
+                        dim3(dm.nblocks), dim3(TX * TY), r.stream, r.P, dm, r.K, r.inv_M, loss,
+                        ws);
         });
     });
     return st;
@@ -506,14 +516,15 @@ template <class OP, int TX, int TY>
 int launch_bwd(const Req& r, const double* dloss, int zc, double* loss) {
     const Dims dm = tile_dims(r.dims, TX, TY, zc);
     // value and gradient in one pass when loss is given
-    int st = loss ? zero_loss(r, loss) : FPDE_OK;
+    double* ws = nullptr;
+    int st = loss ? begin_loss(r, dm.nblocks, loss, &ws) : FPDE_OK;
     if (st != FPDE_OK) return st;
     with_flag(loss != nullptr, [&](auto lo) {
         with_flag(dm.per, [&](auto per) {
             st = launch(bwd_kernel<OP, TX, TY, kBwdReverse, decltype(lo)::value,
                                    decltype(per)::value>,
                         dim3(dm.nblocks), dim3(TX * TY), r.stream, r.P, dm, r.K, dloss,
-                        r.two_over_M, r.inv_M, loss);
+                        r.two_over_M, r.inv_M, loss, ws);
         });
     });
     return st;
@@ -554,7 +565,7 @@ template <class GEO, class OP>
 int launch_fwd3(const Req& r, bool store, double* loss) {
     const bool narrow = !store || r.N * OP::NR * 4 <= (32LL << 20);
     return with_tile<typename GEO::TF, typename GEO::TF2>(
-        r.dims, true, GEO::FWD_PROLOGUE, narrow, [&](auto t, int zc) {
+        r.dims, !r.ws, GEO::FWD_PROLOGUE, narrow, [&](auto t, int zc) {
             using T = decltype(t);
             if constexpr (GEO::FWD_QUEUE)
                 return launch_fwdq<OP, T::TX, T::TY>(r, store, loss, zc);
@@ -565,7 +576,7 @@ int launch_fwd3(const Req& r, bool store, double* loss) {
 template <class GEO, class OP>
 int launch_bwd3(const Req& r, const double* dloss, double* loss) {
     return with_tile<typename GEO::TB, typename GEO::TB2>(
-        r.dims, loss != nullptr, kPrologue, true, [&](auto t, int zc) {
+        r.dims, loss && !r.ws, kPrologue, true, [&](auto t, int zc) {
             using T = decltype(t);
             return launch_bwd<OP, T::TX, T::TY>(r, dloss, zc, loss);
         });
@@ -714,9 +725,36 @@ extern "C" int fpde_op_info(int op, int* ndim, int* n_fields, int* n_consts, int
     return FPDE_OK;
 }
 
+// The workspace of a *_ws4 call: checked against every other argument array, and
+// left unused while the stream is being captured (the graph's replays would read
+// and write it later, when its owner may have given it back or use it itself).
+static int take_workspace(Req* r, double* loss, const double* dloss, float* const* outs, int nout,
+                          void* ws) {
+    if (!ws) return FPDE_ERR_ARG;
+    if ((uintptr_t)ws & 7u) return FPDE_ERR_ALIGN;
+    const size_t bytes = (size_t)r->N * sizeof(float);
+    constexpr size_t wb = kWsDoubles * sizeof(double);
+    static_assert(wb == FPDE_WORKSPACE_BYTES, "the header's size");
+    if (overlaps(ws, wb, loss, sizeof(double)) ||
+        (dloss && overlaps(ws, wb, dloss, sizeof(double))))
+        return FPDE_ERR_ARG;
+    for (int f = 0; f < r->d.nf; ++f)
+        if (overlaps(ws, wb, r->P.f[f], bytes)) return FPDE_ERR_ARG;
+    for (int j = 0; j < r->d.nc; ++j)
+        if (overlaps(ws, wb, r->P.c[j], bytes)) return FPDE_ERR_ARG;
+    for (int o = 0; o < nout; ++o)
+        if (overlaps(ws, wb, outs[o], bytes)) return FPDE_ERR_ARG;
+    hipStreamCaptureStatus cap;
+    if (hipStreamIsCapturing(r->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
+        r->ws = (double*)ws;
+    return FPDE_OK;
+}
+
+// ws: a workspace, or nullptr for a call without one (with_ws false)
 static int fwd_impl(int op, const fpde_grid4* grid, const fpde_coeffs* coeffs,
-                                 const float* const* fields, const float* const* consts,
-                                 float* const* residual_out, double* loss, void* stream) {
+                    const float* const* fields, const float* const* consts,
+                    float* const* residual_out, double* loss, void* stream, bool with_ws = false,
+                    void* ws = nullptr) {
     Req r;
     int st = validate_common(op, grid, coeffs, fields, consts, &r);
     if (st != FPDE_OK) return st;
@@ -733,6 +771,10 @@ static int fwd_impl(int op, const fpde_grid4* grid, const fpde_coeffs* coeffs,
         for (int b = 0; b < r.d.nr; ++b) r.P.out[b] = residual_out[b];
     }
     r.stream = (hipStream_t)stream;
+    if (with_ws) {
+        st = take_workspace(&r, loss, nullptr, residual_out, residual_out ? r.d.nr : 0, ws);
+        if (st != FPDE_OK) return st;
+    }
     return run_fwd(r, residual_out != nullptr, loss);
 }
 
@@ -754,10 +796,10 @@ static int bc_impl(int op, const fpde_grid4* grid, const fpde_coeffs* coeffs,
     return run_bc(r, dloss);
 }
 
-static int value_and_grad_impl(int op, const fpde_grid4* grid,
-                                            const fpde_coeffs* coeffs, const float* const* fields,
-                                            const float* const* consts, const double* dloss,
-                                            double* loss, float* const* grads, void* stream) {
+static int value_and_grad_impl(int op, const fpde_grid4* grid, const fpde_coeffs* coeffs,
+                               const float* const* fields, const float* const* consts,
+                               const double* dloss, double* loss, float* const* grads,
+                               void* stream, bool with_ws = false, void* ws = nullptr) {
     Req r;
     int st = prepare_grad_call(op, grid, coeffs, fields, consts, dloss, grads, stream, &r);
     if (st != FPDE_OK) return st;
@@ -771,6 +813,10 @@ static int value_and_grad_impl(int op, const fpde_grid4* grid,
             return FPDE_ERR_ARG;
     for (int j = 0; j < r.d.nc; ++j)
         if (overlaps(loss, sizeof(double), consts[j], bytes)) return FPDE_ERR_ARG;
+    if (with_ws) {
+        st = take_workspace(&r, loss, dloss, grads, r.d.nf, ws);
+        if (st != FPDE_OK) return st;
+    }
     return run_bwd(r, dloss, loss);
 }
 
@@ -882,6 +928,23 @@ extern "C" int fpde_residual_vjp4(int op, const fpde_grid4* grid, const fpde_coe
                                   const float* const* fields, const float* const* sens,
                                   int accumulate, float* const* grads, void* stream) {
     return vjp_impl(op, grid, coeffs, fields, sens, accumulate, grads, stream);
+}
+
+extern "C" int fpde_residual_fwd_ws4(int op, const fpde_grid4* grid, const fpde_coeffs* coeffs,
+                                     const float* const* fields, const float* const* consts,
+                                     float* const* residual_out, double* loss, void* workspace,
+                                     void* stream) {
+    return fwd_impl(op, grid, coeffs, fields, consts, residual_out, loss, stream, true, workspace);
+}
+
+extern "C" int fpde_residual_value_and_grad_ws4(int op, const fpde_grid4* grid,
+                                                const fpde_coeffs* coeffs,
+                                                const float* const* fields,
+                                                const float* const* consts, const double* dloss,
+                                                double* loss, float* const* grads, void* workspace,
+                                                void* stream) {
+    return value_and_grad_impl(op, grid, coeffs, fields, consts, dloss, loss, grads, stream, true,
+                               workspace);
 }
 
 extern "C" const char* fpde_status_string(int status) {

@@ -11,8 +11,8 @@
 //
 // Forward: one residual per interior node, sum of squares accumulated in a
 // per-thread float64 register, reduced with DPP across the wavefront and through
-// LDS across waves, then ONE float64 atomic add per workgroup (Sec. 2.1 fused
-// stencil, with the loss fused as well).
+// LDS across waves, then ONE float64 atomic add per workgroup, or a sum over
+// slots of a workspace (Sec. 2.1 fused stencil, with the loss fused as well).
 //
 // Backward: gather form of the transposed stencil (Sec. 2.2).  The residuals
 // that the gather needs are recomputed, never read: at step z the workgroup
@@ -112,18 +112,88 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     return v;
 }
 
+// The workgroups' loss sums, added up.  Without a workspace every workgroup adds
+// its sum to *loss, which a fill kernel zeroed: those atomics land on one address
+// and serialise at 12 ns each (an otherwise empty launch of 512-thread workgroups:
+// 2.8 us alone, 4.2 with 256 of them adding, 7.3 with 512, 13.4 with 1024), and the fill
+// costs a launch (2.7 us).  With a workspace (layout below) a workgroup writes its
+// sum to a slot of its own and counts itself on its group's counter (kGroup
+// workgroups); a group's last one adds the group's slots in their order, writes
+// the sum to the group's slot and counts on the root, whose last one writes
+// *loss: 4.2-4.4 us for 16 to 512 workgroups, 5.1 for 4096, and no fill.  The counters are zero
+// again at the end.  Ordering: the slots are written and read by agent-scope
+// accesses (past the XCDs' own L2s), a slot's store has completed (vmcnt 0)
+// before its workgroup counts, and a count returns before the slots are read; an
+// agent-scope release and acquire would write back and invalidate the whole L2 of
+// the XCD for every workgroup.
+constexpr int kGroup = 64, kWsCount = 16, kWsGroup = 2048, kWsPart = 4096;  // (in doubles)
+constexpr int kWsMaxBlocks = kGroup * kGroup;
+static_assert(kWsCount * (kGroup + 1) <= kWsGroup && kWsGroup + kGroup <= kWsPart, "layout");
+constexpr int kWsDoubles = kWsPart + kWsMaxBlocks;
+
+__device__ __forceinline__ void st_agent(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double ld_agent(const double* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double lane_bcast(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// v: this thread's part.  ws: nullptr, or kWsDoubles doubles whose counters
+// (the first kWsGroup) are zero; the launch then has at most kWsMaxBlocks workgroups.
 template <int NT>
-__device__ __forceinline__ void block_atomic_sum(double v, double* dst) {
+__device__ __forceinline__ void block_loss(double v, double* loss, double* ws) {
     __shared__ double part[NT / 64];
     v = wave_sum_f64(v);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (lane == 63) part[w] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
+    if (w != 0) return;
+    double s = 0.0;
 #pragma unroll
-        for (int i = 0; i < NT / 64; ++i) s += part[i];
-        atomicAdd(dst, s);
+    for (int i = 0; i < NT / 64; ++i) s += part[i];
+    const int b = blockIdx.x, n = gridDim.x, g = b / kGroup, ng = (n + kGroup - 1) / kGroup;
+    double* count = loss;  // (no workspace: the sum itself goes there)
+    double add = s;
+    double* slots = nullptr;  // this level's slots, `member` the own one of `members`
+    int member = b - g * kGroup, members = min(kGroup, n - g * kGroup);
+    if (ws) {
+        count = ws + kWsCount * (1 + g);
+        add = 1.0;
+        slots = ws + kWsPart + g * kGroup;
+    }
+    // level 0: the group; 1: the root (one group: none).  `last`: this workgroup is
+    // the last one to count on its level.  (One copy of the atomic serves every case.)
+    bool last = false, root = ng == 1;
+#pragma unroll 1
+    for (;;) {
+        if (last) {
+            s = lane_bcast(wave_sum_f64(lane < members ? ld_agent(slots + lane) : 0.0), 63);
+            if (lane == 0) st_agent(count, 0.0);  // (nobody counts on this level again)
+            if (root) {
+                if (lane == 0) *loss = s;
+                return;
+            }
+            root = true;
+            count = ws;
+            slots = ws + kWsGroup;
+            member = g;
+            members = ng;
+        }
+        double old = 0.0;
+        if (lane == 0) {
+            if (ws) {
+                st_agent(slots + member, s);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            old = atomicAdd(count, add);
+        }
+        if (!ws) return;  // (nothing waits for the atomic)
+        last = lane_bcast(old, 0) == (double)(members - 1);
+        if (!last) return;
     }
 }
 
@@ -390,8 +460,8 @@ struct PlaneStream {
 // step: plane z + RD - 2 streams into the slot of plane z-2 while plane z is
 // evaluated, and the consts come CD - 1 planes ahead into registers.  The sum
 // of squares is accumulated per thread in float64, reduced with DPP across the
-// wavefront and through LDS across waves, then added with ONE float64 atomic
-// per workgroup.
+// wavefront and through LDS across waves, then added over the workgroups
+// (block_loss).
 //
 // RD = 4: the plane queued in a step is read in the next one, and the barrier
 // waits for it (the operators with several fields, whose arithmetic per step
@@ -416,7 +486,8 @@ __device__ __forceinline__ void barrier_after() {
 
 template <class OP, int TX, int TY, bool STORE_R, bool PER, int RD = 4>
 __global__ __launch_bounds__(TX* TY, FPDE_FWD_MINW) void fwd_kernel(Ptrs P, Dims D, KCoef K,
-                                                                    double inv_M, double* loss) {
+                                                                    double inv_M, double* loss,
+                                                                    double* ws) {
     constexpr int DIM = OP::DIM, NF = OP::NF, NC = OP::NC, NR = OP::NR, NT = TX * TY;
     constexpr int NC1 = NC > 0 ? NC : 1;
     constexpr int CD = RD / 2;  // const queue: planes z .. z + CD - 1 in registers
@@ -593,7 +664,7 @@ __global__ __launch_bounds__(TX* TY, FPDE_FWD_MINW) void fwd_kernel(Ptrs P, Dims
     // nothing still streams into LDS when the workgroup's LDS is reused below
     // or handed to the next workgroup
     if constexpr (RD != 4) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    block_atomic_sum<NT>(acc * inv_M, loss);
+    block_loss<NT>(acc * inv_M, loss, ws);
 }
 
 // ---------------------------------------------------------------------------
@@ -615,7 +686,7 @@ __global__ __launch_bounds__(TX* TY, FPDE_FWD_MINW) void fwd_kernel(Ptrs P, Dims
 
 template <class OP, int TX, int TY, int Q, bool STORE_R, bool PER>
 __global__ __launch_bounds__(TX* TY) void fwdq_kernel(Ptrs P, Dims D, KCoef K, double inv_M,
-                                                      double* loss) {
+                                                      double* loss, double* ws) {
     constexpr int DIM = OP::DIM, NF = OP::NF, NC = OP::NC, NR = OP::NR, NT = TX * TY;
     constexpr int NC1 = NC > 0 ? NC : 1;
     constexpr int NV = 2 * DIM - 1;  // centre, x -+ 1 [, y -+ 1]
@@ -726,7 +797,7 @@ __global__ __launch_bounds__(TX* TY) void fwdq_kernel(Ptrs P, Dims D, KCoef K, d
     unroll_seq([&](auto j) __attribute__((always_inline)) {
         if (w + decltype(j)::value < L) step(j, w + decltype(j)::value);
     }, std::make_integer_sequence<int, Q - 1>{});
-    block_atomic_sum<NT>(acc * inv_M, loss);
+    block_loss<NT>(acc * inv_M, loss, ws);
 }
 
 // ---------------------------------------------------------------------------
@@ -740,8 +811,8 @@ __global__ __launch_bounds__(TX* TY) void fwdq_kernel(Ptrs P, Dims D, KCoef K, d
 // LOSS: the value and the gradient in one pass.  Every residual of the chunk's
 // planes is evaluated here anyway (own column, once per step), so the kernel
 // also adds their squares to the loss as the forward does (float32 sum over
-// the equations, float64 accumulation, one float64 atomic per workgroup onto
-// *loss, which the host zeroes first): the fields are read once for both.
+// the equations, float64 accumulation, block_loss over the workgroups): the
+// fields are read once for both.
 
 // Waves per SIMD asked for: 512-thread tiles of several fields run two to a CU
 // (their LDS allows it), which needs four waves of at most 128 VGPRs per SIMD.
@@ -752,7 +823,8 @@ template <class OP, int TX, int TY, bool REV, bool LOSS, bool PER>
 __global__ __launch_bounds__(TX* TY, (kBwdMinW<OP, TX * TY>)) void bwd_kernel(Ptrs P, Dims D, KCoef K,
                                                                     const double* dloss,
                                                                     double two_over_M,
-                                                                    double inv_M, double* loss) {
+                                                                    double inv_M, double* loss,
+                                                                    double* ws) {
     constexpr int DIM = OP::DIM, NF = OP::NF, NC = OP::NC, NR = OP::NR, NT = TX * TY;
     constexpr int NC1 = NC > 0 ? NC : 1, NG = OP::NG, NG1 = NG > 0 ? NG : 1;
     constexpr int HY = (DIM == 3) ? 2 : 0;   // field-slot halo (y)
@@ -1024,7 +1096,7 @@ __global__ __launch_bounds__(TX* TY, (kBwdMinW<OP, TX * TY>)) void bwd_kernel(Pt
     if (w < L) step(IC<0>{}, w);
     if (w + 1 < L) step(IC<1>{}, w + 1);
     if (w + 2 < L) step(IC<2>{}, w + 2);
-    if (LOSS) block_atomic_sum<NT>(acc * inv_M, loss);
+    if (LOSS) block_loss<NT>(acc * inv_M, loss, ws);
 }
 
 // ---------------------------------------------------------------------------
