@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "fpde.h"
@@ -19,7 +20,6 @@ namespace {
 // forward and the backward get the same one (256^3), the backward, which marches
 // each chunk top down, starts on the planes the forward read last (still in the
 // memory-side infinity cache).
-// 2-D grids: chunks sized for about kTargetBlocks2 workgroups per launch.
 // backward tile widths: a tile's x-halo columns sit in cache lines of the
 // neighbouring tiles, which L2 serves only while the two tiles march in step;
 // wider tiles have fewer such lines per node
@@ -48,11 +48,11 @@ namespace {
 #ifndef FPDE_HEAT_BWD_TY
 #define FPDE_HEAT_BWD_TY 8
 #endif
+// 2-D rows of the LDS marches (explicit-sensitivity backward; the checking
+// build's backward) and of the register-queue forward (the wide ones)
 #ifndef FPDE_TX2
 #define FPDE_TX2 256
 #endif
-// 2-D forward rows: the loss atomics of a short launch arrive together and are
-// serialised on one address, so the forward uses fewer, wider workgroups
 #ifndef FPDE_TX2_FWD
 #define FPDE_TX2_FWD 1024
 #endif
@@ -74,23 +74,18 @@ namespace {
 #ifndef FPDE_HEAT_FWD_RING
 #define FPDE_HEAT_FWD_RING 8
 #endif
-// 2-D backward: the LDS march (bwd_kernel with one-row tiles); the checking
-// build takes the register-queue march (bwdq_kernel: no LDS, no barrier; NW
-// waves of 62 output columns, Q rows in registers) as a second algorithm whose
-// gradients must match bit for bit.  (The queue march is no faster for the
-// product: NS-2D 2048^2 37.8 against 36.7 us per step.)
+// 2-D backward, and one-pass value and gradient: the register-queue march
+// (bwdq_kernel: no LDS, no barrier; NW waves of 62 output columns, Q rows in
+// registers); the checking build takes the LDS march (bwd_kernel with one-row
+// tiles) as a second algorithm whose gradients must match bit for bit
 #ifndef FPDE_BWD2_QUEUE
-#define FPDE_BWD2_QUEUE 0
+#define FPDE_BWD2_QUEUE 1
 #endif
 #ifndef FPDE_BWD2_NW
 #define FPDE_BWD2_NW 4
 #endif
 #ifndef FPDE_BWD2_Q
 #define FPDE_BWD2_Q 7
-#endif
-// 2-D one-pass value and gradient (the backward with the loss atomics)
-#ifndef FPDE_TX2_VG
-#define FPDE_TX2_VG 512
 #endif
 // explicit-sensitivity backward tiles (3-D)
 #ifndef FPDE_VJP_TX3
@@ -105,15 +100,10 @@ namespace {
 #ifndef FPDE_VJP_HEAT_TY
 #define FPDE_VJP_HEAT_TY 8
 #endif
-#ifndef FPDE_BLOCKS2
-#define FPDE_BLOCKS2 1024
-#endif
 // The backward marches each chunk top-down (see above).
 #ifndef FPDE_BWD_REVERSE
 #define FPDE_BWD_REVERSE 1
 #endif
-constexpr int kTX2 = FPDE_TX2, kTX2F = FPDE_TX2_FWD, kTX2V = FPDE_TX2_VG,
-              kTargetBlocks2 = FPDE_BLOCKS2;
 constexpr bool kBwdReverse = FPDE_BWD_REVERSE != 0;
 
 // planes' worth of time that a chunk's march spends before its first step
@@ -144,11 +134,26 @@ struct Geo3 {
     using TV = V;
     using TV2 = V2;
 };
-// 2-D grids: one-row tiles of kTX2 nodes for every kernel
+// 2-D grids: row segments (TY = 1).  The register-queue kernels start with Q - 1
+// rows in flight, about as long as five steps; RF, RF2, RB: workgroups of the wide
+// and the narrow forward and of the backward per CU (by their VGPRs).  The wide
+// forward wins where the narrow one's loss atomics would be more (NS-2D 2048^2
+// without a workspace: 15.2 us in 256 workgroups of 1024, 17.7 in 512 of 256); the
+// narrow one on short rows and small grids (374 x 447: 7.9 and 7.0 us; Burgers
+// 128 x 256: 5.9 and 4.7, 5.5 of each the launches), and with a workspace
+// (Helmholtz 1024^2: 8.0 and 7.4).
+template <int RF, int RF2, int RB>
 struct Geo2 {
     static constexpr bool D3 = false;
-    static constexpr bool FWD_QUEUE = true;  // (the 2-D forward is always fwdq_kernel)
+    static constexpr double PROLOGUE = 5.0;
+    using TF = Tile<FPDE_TX2_FWD, 1, RF>;
+    using TF2 = Tile<256, 1, RF2, 98>;
+    using TB = Tile<62 * FPDE_BWD2_NW, 1, RB>;
+    using TV = Tile<FPDE_TX2, 1, 4>;
+    using TV2 = TV;
 };
+using Geo2One = Geo2<2, 8, 8>;  // one field: up to 64 VGPRs (the value and gradient 78)
+using Geo2NS = Geo2<1, 4, 3>;   // three: 120, backward 152
 // several fields with nonlinear coupling (NS): two 512-thread forward workgroups
 // per CU (57 KB of LDS each), one 1024-thread backward (148 KB) or two 512-thread
 // ones (79 KB), two 256-thread explicit-sensitivity ones (57 KB).  The narrow
@@ -195,13 +200,13 @@ struct OpTag {
 template <class F>
 int with_op(int op, F&& f) {
     switch (op) {
-    case FPDE_BURGERS_1DT: return f(OpTag<OpBurgers, Geo2>{});
-    case FPDE_HELMHOLTZ_2D: return f(OpTag<OpHelmholtz, Geo2>{});
+    case FPDE_BURGERS_1DT: return f(OpTag<OpBurgers, Geo2One>{});
+    case FPDE_HELMHOLTZ_2D: return f(OpTag<OpHelmholtz, Geo2One>{});
     case FPDE_HEAT_3D_BE: return f(OpTag<OpHeat, GeoHeat>{});
-    case FPDE_NS_2D_STEADY: return f(OpTag<OpNS2, Geo2>{});
+    case FPDE_NS_2D_STEADY: return f(OpTag<OpNS2, Geo2NS>{});
     case FPDE_NS_3D_BE: return f(OpTag<OpNS3, GeoNS3>{});
     case FPDE_NS_3D_STEADY: return f(OpTag<OpNS3S, GeoNS3>{});
-    case FPDE_POISSON_2D: return f(OpTag<OpPoisson<2>, Geo2>{});
+    case FPDE_POISSON_2D: return f(OpTag<OpPoisson<2>, Geo2One>{});
     case FPDE_POISSON_3D: return f(OpTag<OpPoisson<3>, GeoHeat>{});
     case FPDE_NS_2DT: return f(OpTag<OpNST, GeoNS3>{});
     // 3D+t: the 3-D marches run on one time level per workgroup
@@ -364,7 +369,7 @@ Dims tile_dims(const Dims& n, int TX, int TY, int zc) {
     return dm;
 }
 
-// Chunk length of a 3-D march with TX x TY tiles of which RES workgroups fit a
+// Chunk length of a march with TX x TY tiles of which RES workgroups fit a
 // CU at once.  A launch runs in rounds of CUs * RES workgroups, each as long as
 // one chunk's march (its planes plus about kPrologue planes' worth of prologue:
 // the first planes' latency and the halo planes' residuals), so a launch a little over a whole
@@ -373,9 +378,16 @@ Dims tile_dims(const Dims& n, int TX, int TY, int zc) {
 // the 2D+t one at 33 x 201 x 259 28 us in 312 and 20 us in 234.  The rule takes,
 // among the chunk counts that just fill 1, 2, ... CUs' worth of workgroups, the
 // one with the shortest estimated march.  In a last round with k of RES
-// workgroups per CU a step costs 0.3 + 0.7 k / RES of a full round's (128^3,
-// two per CU: 0.67 at one).  A loss without a workspace adds one atomic per
-// workgroup of the last round, serialised at 12 ns, about 0.015 of a step (`loss`).
+// workgroups per CU a step of an LDS march costs 0.3 + 0.7 k / RES of a full
+// round's, the fullest CU deciding (NS-3D, two per CU: 0.65 at one; heat 97 x 90 x 41
+// backward 6.3 us in 228 workgroups, 7.2 in 288); one of a register-queue march,
+// whose waves wait for nobody, max(0.25 + 0.75 / RES, 0.1 + 0.9 k / RES), its
+// latency or its throughput (2-D backward, eight per CU, us per row at 1, 2, 3.8,
+// 6.5 and 8: 0.22, 0.26, 0.40, 0.66, 0.8).
+// A loss costs one atomic per workgroup of the last round, serialised at 12 ns,
+// about 0.015 of a step, or through a workspace a second level of slots beyond 64
+// workgroups, about 1 us or 0.8 of a step.
+enum class Sum { none, atomics, workspace };
 #ifndef FPDE_CUS
 #define FPDE_CUS 256
 #endif
@@ -384,38 +396,36 @@ struct Chunks {
     int zc;       // planes per chunk
     double cost;  // estimated time, in steps of a full round
 };
-Chunks plan_chunks(const Dims& n, int TX, int TY, int res, bool loss, double prologue = kPrologue) {
+Chunks plan_chunks(const Dims& n, int TX, int TY, int res, Sum sum, double prologue,
+                   bool queue = false) {
     const long long tiles =
         (long long)((n.nx + TX - 1) / TX) * ((n.ny + TY - 1) / TY) * n.nlev;
     const int nplanes = n.nz - 2 * n.zlo;
     Chunks best = {nplanes, 0.0};
     long long tried = 0;
-    // CU loads 1 .. res (one round, in part), then whole rounds up to 8
-    for (int j = 1; j <= res + 7; ++j) {
-        const long long load = j <= res ? j : (long long)(j - res + 1) * res;
-        long long nch = load * kCUs / tiles;
+    // an eighth, a quarter, half of the CUs; CU loads 1 .. res (one round, in
+    // part); then whole rounds up to 8
+    for (int j = -2; j <= res + 7; ++j) {
+        const long long slots = j <= 0      ? kCUs >> (1 - j)
+                                : j <= res ? (long long)j * kCUs
+                                           : (long long)(j - res + 1) * res * kCUs;
+        long long nch = slots / tiles;
         nch = nch < 1 ? 1 : nch > nplanes ? nplanes : nch;
         if (nch == tried) continue;
         tried = nch;
         const int zc = (int)((nplanes + nch - 1) / nch);
         const long long W = tiles * ((nplanes + zc - 1) / zc);
-        const long long slots = (long long)kCUs * res, full = W / slots;
-        const long long k = (W - full * slots + kCUs - 1) / kCUs;
-        double cost = (zc + prologue) * ((double)full + (k ? 0.3 + 0.7 * (double)k / res : 0.0));
-        if (loss) cost += 0.015 * (double)(W < slots ? W : slots);
-        if (j == 1 || cost < best.cost) best = {zc, cost};
+        const long long round = (long long)kCUs * res, full = W / round;
+        const long long rest = W - full * round;
+        const double k = queue ? (double)rest / kCUs : (double)((rest + kCUs - 1) / kCUs);
+        const double last = queue ? std::max(0.25 + 0.75 / res, 0.1 + 0.9 * k / res)
+                                  : 0.3 + 0.7 * k / res;
+        double cost = (zc + prologue) * ((double)full + (rest ? last : 0.0));
+        if (sum == Sum::atomics) cost += 0.015 * (double)(W < round ? W : round);
+        if (sum == Sum::workspace && W > kGroup) cost += 0.8;
+        if (best.cost == 0.0 || cost < best.cost) best = {zc, cost};
     }
     return best;
-}
-
-// 2-D grids: chunk length giving about `target` workgroups (a chunk holds at
-// least one row)
-int chunk_rows(const Dims& n, int TX, int target) {
-    const long long tiles = (n.nx + TX - 1) / TX;
-    const int nrows = n.nz - 2 * n.zlo;
-    long long nch = (target + tiles - 1) / tiles;
-    if (nch > nrows) nch = nrows;
-    return (int)((nrows + nch - 1) / nch);
 }
 
 int check_outputs(const Req& r, const fpde_grid4*, const float* const* fields,
@@ -530,28 +540,35 @@ int launch_bwd(const Req& r, const double* dloss, int zc, double* loss) {
     return st;
 }
 
-// 2-D register-queue backward (the gradient alone)
+// 2-D register-queue backward (with the loss when given)
 template <class OP>
-int launch_bwdq(const Req& r, const double* dloss, int zc) {
+int launch_bwdq(const Req& r, const double* dloss, int zc, double* loss) {
     constexpr int NW = FPDE_BWD2_NW;
     const Dims dm = tile_dims(r.dims, 62 * NW, 1, zc);
-    int st = FPDE_OK;
-    with_flag(dm.per, [&](auto per) {
-        st = launch(bwdq_kernel<OP, NW, FPDE_BWD2_Q, decltype(per)::value>, dim3(dm.nblocks),
-                    dim3(64 * NW), r.stream, r.P, dm, r.K, dloss, r.two_over_M);
+    double* ws = nullptr;
+    int st = loss ? begin_loss(r, dm.nblocks, loss, &ws) : FPDE_OK;
+    if (st != FPDE_OK) return st;
+    with_flag(loss != nullptr, [&](auto lo) {
+        with_flag(dm.per, [&](auto per) {
+            st = launch(bwdq_kernel<OP, NW, FPDE_BWD2_Q, decltype(lo)::value, decltype(per)::value>,
+                        dim3(dm.nblocks), dim3(64 * NW), r.stream, r.P, dm, r.K, dloss,
+                        r.two_over_M, r.inv_M, loss, ws);
+        });
     });
     return st;
 }
 
-int zc2(const Req& r) { return chunk_rows(r.dims, kTX2, kTargetBlocks2); }
+Sum loss_sum(const Req& r, const double* loss) {
+    return !loss ? Sum::none : r.ws ? Sum::workspace : Sum::atomics;
+}
 
 // f(Tile<...>{}, zc) for the wide tile A or (if narrow) the narrow tile B of a
 // 3-D launch, whichever has the shorter estimated march (plan_chunks)
-template <class A, class B, class F>
-int with_tile(const Dims& n, bool loss, double prologue, bool narrow, F&& f) {
-    const Chunks a = plan_chunks(n, A::TX, A::TY, A::RES, loss, prologue);
+template <class A, class B, bool QUEUE = false, class F>
+int with_tile(const Dims& n, Sum sum, double prologue, bool narrow, F&& f) {
+    const Chunks a = plan_chunks(n, A::TX, A::TY, A::RES, sum, prologue, QUEUE);
     if (!std::is_same<A, B>::value && narrow) {
-        const Chunks b = plan_chunks(n, B::TX, B::TY, B::RES, loss, prologue);
+        const Chunks b = plan_chunks(n, B::TX, B::TY, B::RES, sum, prologue, QUEUE);
         if (b.cost * B::STEP < a.cost * A::STEP) return f(B{}, b.zc);
     }
     return f(A{}, a.zc);
@@ -564,8 +581,8 @@ int with_tile(const Dims& n, bool loss, double prologue, bool narrow, F&& f) {
 template <class GEO, class OP>
 int launch_fwd3(const Req& r, bool store, double* loss) {
     const bool narrow = !store || r.N * OP::NR * 4 <= (32LL << 20);
-    return with_tile<typename GEO::TF, typename GEO::TF2>(
-        r.dims, !r.ws, GEO::FWD_PROLOGUE, narrow, [&](auto t, int zc) {
+    return with_tile<typename GEO::TF, typename GEO::TF2, GEO::FWD_QUEUE>(
+        r.dims, loss_sum(r, loss), GEO::FWD_PROLOGUE, narrow, [&](auto t, int zc) {
             using T = decltype(t);
             if constexpr (GEO::FWD_QUEUE)
                 return launch_fwdq<OP, T::TX, T::TY>(r, store, loss, zc);
@@ -576,10 +593,31 @@ int launch_fwd3(const Req& r, bool store, double* loss) {
 template <class GEO, class OP>
 int launch_bwd3(const Req& r, const double* dloss, double* loss) {
     return with_tile<typename GEO::TB, typename GEO::TB2>(
-        r.dims, loss && !r.ws, kPrologue, true, [&](auto t, int zc) {
+        r.dims, loss_sum(r, loss), kPrologue, true, [&](auto t, int zc) {
             using T = decltype(t);
             return launch_bwd<OP, T::TX, T::TY>(r, dloss, zc, loss);
         });
+}
+
+// 2-D launches
+template <class GEO, class OP>
+int launch_fwd2(const Req& r, bool store, double* loss) {
+    return with_tile<typename GEO::TF, typename GEO::TF2, true>(
+        r.dims, loss_sum(r, loss), GEO::PROLOGUE, true, [&](auto t, int zc) {
+            return launch_fwdq<OP, decltype(t)::TX, 1>(r, store, loss, zc);
+        });
+}
+template <class GEO, class OP>
+int launch_bwd2(const Req& r, const double* dloss, double* loss) {
+    using T = typename GEO::TB;
+    if constexpr (FPDE_BWD2_QUEUE) {
+        const int zc =
+            plan_chunks(r.dims, T::TX, 1, T::RES, loss_sum(r, loss), GEO::PROLOGUE, true).zc;
+        return launch_bwdq<OP>(r, dloss, zc, loss);
+    } else {
+        const int zc = plan_chunks(r.dims, FPDE_TX2, 1, 4, loss_sum(r, loss), kPrologue).zc;
+        return launch_bwd<OP, FPDE_TX2, 1>(r, dloss, zc, loss);
+    }
 }
 
 template <class OP>
@@ -633,15 +671,11 @@ int run_vjp(const Req& r, bool acc) {
     return with_op(r.op, [&](auto tag) {
         using OP = typename decltype(tag)::OP;
         using GEO = typename decltype(tag)::GEO;
-        if constexpr (GEO::D3) {
-            return with_tile<typename GEO::TV, typename GEO::TV2>(
-                base, false, kPrologue, true, [&](auto t, int zc) {
-                    using T = decltype(t);
-                    return launch_vjp<OP, T::TX, T::TY>(r, acc, base, zc);
-                });
-        } else {
-            return launch_vjp<OP, kTX2, 1>(r, acc, base, chunk_rows(base, kTX2, kTargetBlocks2));
-        }
+        return with_tile<typename GEO::TV, typename GEO::TV2>(
+            base, Sum::none, kPrologue, true, [&](auto t, int zc) {
+                using T = decltype(t);
+                return launch_vjp<OP, T::TX, T::TY>(r, acc, base, zc);
+            });
     });
 }
 
@@ -654,7 +688,7 @@ int run_fwd(const Req& r0, bool store, double* loss) {
         if constexpr (GEO::D3)
             return launch_fwd3<GEO, OP>(r, store, loss);
         else
-            return launch_fwdq<OP, kTX2F, 1>(r, store, loss, zc2(r));
+            return launch_fwd2<GEO, OP>(r, store, loss);
     });
 }
 
@@ -680,12 +714,8 @@ int run_bwd(const Req& r0, const double* dloss, double* loss = nullptr) {
             return st;
         } else if constexpr (GEO::D3)
             return launch_bwd3<GEO, OP>(r, dloss, loss);
-        else if (loss)
-            return launch_bwd<OP, kTX2V, 1>(r, dloss, zc2(r), loss);
-        else if (FPDE_BWD2_QUEUE)
-            return launch_bwdq<OP>(r, dloss, zc2(r));
         else
-            return launch_bwd<OP, kTX2, 1>(r, dloss, zc2(r), loss);
+            return launch_bwd2<GEO, OP>(r, dloss, loss);
     });
 }
 

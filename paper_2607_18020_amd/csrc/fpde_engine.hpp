@@ -1110,7 +1110,10 @@ __global__ __launch_bounds__(TX* TY, (kBwdMinW<OP, TX * TY>)) void bwd_kernel(Pt
 // shift by one lane brings them over.  So that every lane has both neighbours,
 // the two edge lanes of each wave evaluate residuals only (at the columns
 // before and after the wave's 62 output columns), and a workgroup of NW waves
-// writes 62 NW columns.  Every node of the marched rows is written once, the
+// writes 62 NW columns.  Against the LDS march, each over its best chunk length
+// (us): NS-2D 2048^2 20.1 and 20.1, 1124 x 1780 11.1 and 12.6, 374 x 447 4.7 and
+// 5.4; Helmholtz 2048^2 12.0 and 13.0, 1024^2 6.0 and 6.1; its step is the shorter
+// (0.27 us at one workgroup per CU, 0.64 with the barrier), so it needs fewer of them.  Every node of the marched rows is written once, the
 // boundary columns included (R is zero off the residual set); no atomics.
 
 // v of lane i - 1 (wave_shr:1) or of lane i + 1 (wave_shl:1); the lanes at the
@@ -1122,9 +1125,11 @@ __device__ __forceinline__ float lane_next(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, false));
 }
 
-template <class OP, int NW, int Q, bool PER>
+// LOSS: the value and the gradient in one pass, as in bwd_kernel.
+template <class OP, int NW, int Q, bool LOSS, bool PER>
 __global__ __launch_bounds__(NW * 64) void bwdq_kernel(Ptrs P, Dims D, KCoef K, const double* dloss,
-                                                     double two_over_M) {
+                                                     double two_over_M, double inv_M,
+                                                     double* loss, double* ws) {
     constexpr int NF = OP::NF, NC = OP::NC, NR = OP::NR, NG = OP::NG;
     constexpr int NC1 = NC > 0 ? NC : 1, NG1 = NG > 0 ? NG : 1;
     constexpr int TXO = 62 * NW;  // output columns per workgroup
@@ -1191,6 +1196,7 @@ __global__ __launch_bounds__(NW * 64) void bwdq_kernel(Ptrs P, Dims D, KCoef K, 
     r_row(IC<0>{}, IC<1>{}, IC<2>{}, z0 - 1, Rm, Sm);
     r_row(IC<1>{}, IC<2>{}, IC<3>{}, z0, Rc, Sc);
 
+    double acc = 0.0;  // LOSS: sum of squares of the output columns' residuals
     auto step = [&](auto jc, int w) __attribute__((always_inline)) {
         constexpr int J = decltype(jc)::value;  // w % Q
         // slots of the rows z - 1, z, z + 1, z + 2 (k = w + 1 .. w + 4), and of the row
@@ -1218,6 +1224,12 @@ __global__ __launch_bounds__(NW * 64) void bwdq_kernel(Ptrs P, Dims D, KCoef K, 
             rs[b].m[1] = lane_prev(Rc[b]);
             rs[b].p[1] = lane_next(Rc[b]);
         }
+        if (LOSS) {  // R of this row, zero off the residual set
+            float ss = 0.f;
+#pragma unroll
+            for (int b = 0; b < NR; ++b) ss = fmaf(Rc[b], Rc[b], ss);
+            acc += (double)(out_lane ? ss : 0.f);
+        }
         float g[NF];
         OP::gather_rest(fs, rs, Sc, K, g);
         const int zr = PER ? wrap_idx(z, D.nz) : z;
@@ -1241,6 +1253,7 @@ __global__ __launch_bounds__(NW * 64) void bwdq_kernel(Ptrs P, Dims D, KCoef K, 
     unroll_seq([&](auto j) __attribute__((always_inline)) {
         if (w + decltype(j)::value < L) step(j, w + decltype(j)::value);
     }, std::make_integer_sequence<int, Q - 1>{});
+    if constexpr (LOSS) block_loss<NW * 64>(acc * inv_M, loss, ws);
 }
 
 // ---------------------------------------------------------------------------

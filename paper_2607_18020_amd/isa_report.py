@@ -160,9 +160,12 @@ def _template_args(name: str) -> List[str]:
 
 def reduces_loss(name: str) -> bool:
     """The kernels that add a float64 partial loss per workgroup: every forward,
-    and the backward with its LOSS flag (bwd_kernel<OP, TX, TY, REV, LOSS, PER>)."""
+    and the backwards with their LOSS flag (bwd_kernel<OP, TX, TY, REV, LOSS, PER>,
+    bwdq_kernel<OP, NW, Q, LOSS, PER>)."""
     if name.startswith(("fwd_kernel", "fwdq_kernel")):
         return True
+    if name.startswith("bwdq_kernel"):
+        return _template_args(name)[3] == "true"
     return name.startswith("bwd_kernel") and _template_args(name)[4] == "true"
 
 
