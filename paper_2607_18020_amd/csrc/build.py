@@ -47,8 +47,8 @@ CHECK_FLAGS = [
     "-DFPDE_CUS=90", "-DFPDE_HEAT_FWD_TX=128", "-DFPDE_HEAT_BWD_TX=128",
     "-DFPDE_VJP_TY3=8", "-DFPDE_VJP_HEAT_TX=64",
     "-DFPDE_TX2=128", "-DFPDE_TX2_FWD=512",
-    "-DFPDE_FWD2_Q=4", "-DFPDE_HEAT_FWD_QUEUE=1", "-DFPDE_NS4_BWD_TX=64", "-DFPDE_NS4_BWD_TY=8",
-    "-DFPDE_BWD2_QUEUE=0", "-DFPDE_TM_REMAP=1",
+    "-DFPDE_FWD2_Q=4", "-DFPDE_HEAT_FWD_QUEUE=1", "-DFPDE_T4_CHECK",
+    "-DFPDE_BWD2_QUEUE=0",
 ]
 
 _NOISE = "is not a recognized feature for this target"

@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <tuple>
 #include <type_traits>
 
 #include "fpde.h"
@@ -165,18 +166,25 @@ using Geo2NS = Geo2<1, 4, 3>;   // three: 120, backward 152
 using GeoNS3 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>, Tile<64, 8, 2, 104>,
                     Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>, Tile<64, 8, 2, 106>,
                     Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>, Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
-// 3D+t NS: the level march reads six time-neighbour velocities per node besides
-// the four fields, which do not fit the 128 registers of a 1024-thread backward
-// tile: 768-thread wide backward tiles (at 20 x 128^3, 5% faster than 512
-// threads), 512-thread narrow ones, one to a CU
-#ifndef FPDE_NS4_BWD_TX
-#define FPDE_NS4_BWD_TX 128
+// 3D+t NS: the forward and the explicit-sensitivity backward run the 3-D marches
+// on one time level per workgroup; the backward marches time (bwdt_kernel) over
+// blocks of TZ x TY x TX nodes with NT threads.  STEP: one level's time, percent of
+// the first one's (4.75, 6.3, 3.75 us on an idle chip, 6.2, 8.7, 4.65 on a full one);
+// launch_bwdt takes the block with the shortest estimated march: the larger ones
+// evaluate fewer residuals per node (1.65, 1.56, 1.81), the smaller ones fill more
+// CUs.  Backward at 20 x 128^3 710, 656, 705 us; 14 x 56 x 55 x 83 70, 81, 79;
+// 22 x 29 x 32 x 28 29, 31, 24 (815, 102, 66 with a level march and a time pass).
+template <int TZ_, int TY_, int TX_, int NT_, int STEP_>
+struct Block4 {
+    static constexpr int TZ = TZ_, TY = TY_, TX = TX_, NT = NT_, STEP = STEP_;
+};
+#ifdef FPDE_T4_CHECK
+using Blocks4 = std::tuple<Block4<4, 4, 64, 1024, 100>>;
+#else
+using Blocks4 =
+    std::tuple<Block4<8, 6, 32, 768, 100>, Block4<8, 8, 32, 512, 140>, Block4<4, 8, 32, 1024, 75>>;
 #endif
-#ifndef FPDE_NS4_BWD_TY
-#define FPDE_NS4_BWD_TY 6
-#endif
-using GeoNS4 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>, Tile<64, 8, 2, 104>,
-                    Tile<FPDE_NS4_BWD_TX, FPDE_NS4_BWD_TY, 1>, Tile<64, 8, 1, 75>,
+using GeoNS4 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>, Tile<64, 8, 2, 104>, void, void,
                     Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>, Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
 // one field, a Laplacian (heat, Poisson): 1024-thread wide forward and
 // explicit-sensitivity workgroups, the others 512 threads, bound by the 2048
@@ -637,16 +645,51 @@ int launch_bc(const Req& r, const double* dloss) {
     }
 }
 
-// 3D+t: the time part of the backward, one lane per spatial node marching the
-// time levels (after the level march, which wrote the spatial part)
-template <class OP>
-int launch_tm(const Req& r, const double* dloss) {
-    int st = FPDE_OK;
-    with_flag(r.dims.per, [&](auto per) {
-        st = launch(tm_kernel<OP, decltype(per)::value>,
-                    dim3((unsigned)((r.dims.vol + 255) / 256)), dim3(256), r.stream, r.P, r.dims,
-                    r.K, dloss, r.two_over_M);
+// 3D+t: the time-marching backward (with the loss when given).  A chunk of levels
+// evaluates residuals at up to two levels more than it writes: its prologue.
+template <class OP, class T>
+int launch_bwdt_as(const Req& r, const double* dloss, double* loss, int zc) {
+    constexpr int TZ = T::TZ, TY = T::TY, TX = T::TX, NT = T::NT;
+    Dims dm = r.dims;
+    dm.tiles_x = (dm.nx + TX - 1) / TX;
+    dm.tiles_y = (dm.ny + TY - 1) / TY;
+    dm.zc = zc;
+    dm.nblocks = dm.tiles_x * dm.tiles_y * ((dm.nz + TZ - 1) / TZ) * ((dm.nlev + zc - 1) / zc);
+    double* ws = nullptr;
+    int st = loss ? begin_loss(r, dm.nblocks, loss, &ws) : FPDE_OK;
+    if (st != FPDE_OK) return st;
+    with_flag(loss != nullptr, [&](auto lo) {
+        with_flag(dm.per, [&](auto per) {
+            st = launch(bwdt_kernel<OP, TZ, TY, TX, NT, decltype(lo)::value, decltype(per)::value>,
+                        dim3(dm.nblocks), dim3(NT), r.stream, r.P, dm, r.K, dloss, r.two_over_M,
+                        r.inv_M, loss, ws);
+        });
     });
+    return st;
+}
+template <class OP, class... T>
+int launch_bwdt(const Req& r, const double* dloss, double* loss, std::tuple<T...>) {
+    Dims q = {};  // a launch's chunks: those of a march over nlev planes of its blocks
+    q.ny = q.nlev = 1;
+    q.nz = r.dims.nlev;
+    int best = 0, zc = 0, i = 0;
+    double cost = 0.0;
+    auto consider = [&](auto t) {
+        using B = decltype(t);
+        q.nx = ((r.dims.nx + B::TX - 1) / B::TX) * ((r.dims.ny + B::TY - 1) / B::TY) *
+               ((r.dims.nz + B::TZ - 1) / B::TZ);
+        const Chunks c = plan_chunks(q, 1, 1, 1, loss_sum(r, loss), 2.0);
+        if (i == 0 || c.cost * B::STEP < cost) {
+            best = i;
+            zc = c.zc;
+            cost = c.cost * B::STEP;
+        }
+        ++i;
+    };
+    (consider(T{}), ...);
+    int st = FPDE_OK;
+    i = 0;
+    ((i++ == best ? (void)(st = launch_bwdt_as<OP, T>(r, dloss, loss, zc)) : (void)0), ...);
     return st;
 }
 
@@ -697,19 +740,17 @@ int run_fwd(const Req& r0, bool store, double* loss) {
 // every plane: at the end planes the gather with the residuals off the residual
 // set taken as zero is their exact boundary term, so no boundary kernel follows
 //
-// 3D+t grids: the level march covers every plane of each level with residuals
-// (the boundary planes of the level included, as above), the time march then
-// adds the time part, and with the loss the end time levels follow (bc_mode 0).
+// 3D+t grids: the time march covers every level with residuals; with the loss the
+// end time levels follow (bc_mode 0).
 int run_bwd(const Req& r0, const double* dloss, double* loss = nullptr) {
     Req r = r0;
     r.dims = levels(r0.dims, false);
-    if (loss || r.d.time) r.dims.zlo = 0;
+    if (loss) r.dims.zlo = 0;
     return with_op(r.op, [&](auto tag) {
         using OP = typename decltype(tag)::OP;
         using GEO = typename decltype(tag)::GEO;
         if constexpr (OP::TIME) {
-            int st = launch_bwd3<GEO, OP>(r, dloss, loss);
-            if (st == FPDE_OK) st = launch_tm<OP>(r, dloss);
+            int st = launch_bwdt<OP>(r, dloss, loss, Blocks4{});
             if (st == FPDE_OK && loss && !r.dims.per) st = launch_bc<OP>(r, dloss);
             return st;
         } else if constexpr (GEO::D3)

@@ -1502,157 +1502,305 @@ __global__ __launch_bounds__(256) void bc_kernel(Ptrs P, Dims D, KCoef K, const 
 }
 
 // ---------------------------------------------------------------------------
-// 3D+t grids (operators with TIME).  The marching kernels above run on one time
-// level per workgroup: their residuals read the velocities of the neighbouring
-// levels as point values, and their gather is the spatial part of the
-// transposed stencil.  The time part of the gather,
+// 3D+t grids (operators with TIME): the backward marches the TIME axis.  The
+// transposed stencil couples the time levels only at a node itself,
 //     dL/dc_q(n) += (R_q(n - e_t) - R_q(n + e_t)) / (2 h_t),
-// needs residuals of other time levels, which another workgroup evaluates.  So
-// tm_kernel recomputes them: one lane per spatial node marches the time levels
-// and keeps R_q of the levels t - 1, t, t + 1 in registers, so every residual is
-// evaluated once; each node's gradient is read, the time part added, and
-// written once (the march's spatial part is already there).  Only nodes on the
-// spatial residual set have a time part (R is zero off it).
+// so a workgroup owns a TZ x TY x TX block of one level's nodes and walks the
+// levels: the fields of the block and two halo nodes are in LDS for one level at a
+// time, the residuals of the block and its six faces are evaluated into LDS, and
+// what other levels contribute is the node's own: the velocities of t - 1 and
+// t + 1 at each residual position, the residuals of t - 2 and t - 1 and the
+// spatial part of t - 1's gradient at each node, all in registers.  Every node's gradient is
+// formed in one pass and written once.  (Marching the first spatial axis instead,
+// one level per workgroup, the time part needs the residuals of two other levels:
+// a second kernel evaluated them all again and read and rewrote the gradients,
+// 390 + 403 us at 20 x 128^3 for 4.1 GB of traffic; here 656 us, 1.05 GB read and
+// 0.60 GB written.)  What bounds it is arithmetic: about 297 VALU instructions per
+// node and wave, 46% of the cycles, and the phases between its barriers.
 //
-// The residual of level L reads the stars at L and the node's velocities at
-// L -+ 1, which are the centres of the stars at L -+ 1.  The lane loads the stars
-// of each level once, one level ahead of the residual it evaluates, and keeps
-// the stars of L + 1 and the centre velocities of L - 1 in registers: a point
-// value fetched once for a residual and again, a level later, for a star would
-// come from HBM twice, since a whole level of every field passes through L2 in
-// between.
+// Each level's fields come through registers: loaded while the level before is
+// gathered, written to LDS once its gather is done.  LDS holds one level
+// (83 KB of fields and 54 KB of residuals at 8 x 8 x 32), so one workgroup runs
+// per CU, with one to four nodes per thread by what its registers hold (1024 threads
+// with two nodes each would spill; loads a phase earlier changed nothing).
+// A chunk of levels starts and ends with one level whose residuals are evaluated
+// at the block's own nodes only.
+template <int TZ, int TY, int TX, int NT>
+struct TBlock {
+    static constexpr int NODES = TZ * TY * TX, NOWN = NODES / NT;
+    static constexpr int FY = TY + 4, FX = TX + 4, FSZ = (TZ + 4) * FY * FX;  // field box
+    static constexpr int RY = TY + 2, RX = TX + 2, RSZ = (TZ + 2) * RY * RX;  // residual box
+    static constexpr int NFACE = 2 * (TY * TX + TZ * TX + TZ * TY);
+    static constexpr int NRING = (NFACE + NT - 1) / NT, NPOS = NOWN + NRING;
+    // elements loaded: the box without the first two and the last two rows
+    static constexpr int SKIP = 2 * FX, NLOAD = FSZ - 2 * SKIP, KL = (NLOAD + NT - 1) / NT;
+    static_assert(NODES % NT == 0, "whole nodes per thread");
 
-// The stars of every field at one spatial node of level lev (lev in range),
-// loaded through the level's buffer descriptors (o: the node's byte offset in a
-// level, n[6]: its neighbours' at -+ one node along the three spatial axes).
-template <class OP>
-__device__ __forceinline__ void stars_at_level(const Ptrs& P, int lev, uint32_t vbytes, uint32_t o,
-                                               const uint32_t* n, Star* st) {
-    constexpr int NF = OP::NF, D3 = OP::D;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-        const __amdgpu_buffer_rsrc_t r = plane_rsrc(P.f[f], lev, vbytes);
-        st[f].c = f < D3 ? bld(r, o) : 0.f;  // (the pressure's own value enters no residual)
-#pragma unroll
-        for (int a = 0; a < D3; ++a) {
-            st[f].m[a] = bld(r, n[2 * a]);
-            st[f].p[a] = bld(r, n[2 * a + 1]);
-        }
-    }
-}
-
-// Lanes: one per spatial node of a level, 256 consecutive nodes per workgroup,
-// in launch order or (FPDE_TM_REMAP) XCD-contiguous.  Each lane marches the
-// time levels on its own, so the rows that neighbouring workgroups share meet
-// in L2 only while those workgroups run at the same time.  At 20 x 128^3 this
-// order was the fastest of the lane blocks tried (2 x 2 x 64 up to 4 x 4 x 64
-// nodes, and 128-wide blocks of 1 to 8 rows: 1-8% slower), and the
-// XCD-contiguous order 3-4% slower; unlike a block, it leaves no lane idle
-// whatever the extent of the last axis.
-#ifndef FPDE_TM_REMAP
-#define FPDE_TM_REMAP 0
-#endif
-
-template <class OP, bool PER>
-__global__ __launch_bounds__(256) void tm_kernel(Ptrs P, Dims D, KCoef K, const double* dloss,
-                                                 double two_over_M) {
-    constexpr int NF = OP::NF, D3 = OP::D;
-    static_assert(OP::NC == 2 * D3, "consts: the velocities at t - 1, then at t + 1");
-    const int blk = FPDE_TM_REMAP ? remap_xcd((int)blockIdx.x, (int)gridDim.x) : (int)blockIdx.x;
-    const int idx = blk * 256 + (int)threadIdx.x;  // (vol < 2^29)
-    if (idx >= (int)D.vol) return;
-    const int i3 = idx % D.nx, r = idx / D.nx, i2 = r % D.ny, i1 = r / D.ny;
-    if (!PER && !(i1 >= 1 && i1 <= D.nz - 2 && i2 >= 1 && i2 <= D.ny - 2 && i3 >= 1 &&
-                  i3 <= D.nx - 2))
-        return;  // off the spatial residual set: no time part
-    const uint32_t vbytes = (uint32_t)D.vol * 4u;
-    const uint32_t o = (uint32_t)idx * 4u;
-    // neighbours along x (array axis 1), y, z: -+1, wrapped on a periodic grid
-    uint32_t n[6];
-    {
-        const int sx = D.ny * D.nx, sy = D.nx;
-        auto at = [&](int a1, int a2, int a3) -> uint32_t {
-            if (PER) {
-                a1 = wrap_idx(a1, D.nz);
-                a2 = wrap_idx(a2, D.ny);
-                a3 = wrap_idx(a3, D.nx);
-            }
-            return (uint32_t)(a1 * sx + a2 * sy + a3) * 4u;
-        };
-        n[0] = at(i1 - 1, i2, i3);
-        n[1] = at(i1 + 1, i2, i3);
-        n[2] = at(i1, i2 - 1, i3);
-        n[3] = at(i1, i2 + 1, i3);
-        n[4] = at(i1, i2, i3 - 1);
-        n[5] = at(i1, i2, i3 + 1);
-    }
-    const float scale = (float)(two_over_M * (*dloss));
-    // levels whose gradient gets the time part: those the march wrote (all of
-    // them on a periodic grid, else 1 .. nt - 2, whose residual neighbours are
-    // the levels 0 .. nt - 1 with R zero at the end levels); nt >= 3
-    const int t0 = PER ? 0 : 1, t1 = PER ? D.nt - 1 : D.nt - 2;
-    // the march state: the next residual is that of level L, from the stars of
-    // L (sc) and the centre velocities of L - 1 (vm) and L + 1 (loaded with the
-    // stars of L + 1, which become sc for the next level)
-    int L;
-    Star sc[NF];
-    float vm[D3];
-    auto next_R = [&](float* R) __attribute__((always_inline)) {
-        if (!PER && L > D.nt - 2) {  // level nt - 1: R = 0 and no level beyond it
-#pragma unroll
-            for (int q = 0; q < D3; ++q) R[q] = 0.f;
-            ++L;
+    __device__ static void face(int r, int& z, int& y, int& x) {  // face node -> block position
+        if (r < 2 * TY * TX) {
+            z = r < TY * TX ? -1 : TZ;
+            r %= TY * TX;
+            y = r / TX;
+            x = r % TX;
             return;
         }
-        Star sn[NF];
-        stars_at_level<OP>(P, PER ? wrap_idx(L + 1, D.nt) : L + 1, vbytes, o, n, sn);
-        float c[2 * D3], Rf[OP::NR];
-#pragma unroll
-        for (int b = 0; b < D3; ++b) {
-            c[b] = vm[b];
-            c[D3 + b] = sn[b].c;
+        r -= 2 * TY * TX;
+        if (r < 2 * TZ * TX) {
+            y = r < TZ * TX ? -1 : TY;
+            r %= TZ * TX;
+            z = r / TX;
+            x = r % TX;
+            return;
         }
-        OP::residual(sc, c, K, Rf);
-#pragma unroll
-        for (int q = 0; q < D3; ++q) {
-            R[q] = Rf[q];
-            vm[q] = sc[q].c;
+        r -= 2 * TZ * TX;
+        x = r < TZ * TY ? -1 : TX;
+        r %= TZ * TY;
+        z = r / TY;
+        y = r % TY;
+    }
+};
+
+template <class OP, int TZ, int TY, int TX, int NT, bool LOSS, bool PER>
+__global__ __launch_bounds__(NT) void bwdt_kernel(Ptrs P, Dims D, KCoef K, const double* dloss,
+                                                    double two_over_M, double inv_M, double* loss,
+                                                    double* ws) {
+    using T = TBlock<TZ, TY, TX, NT>;
+    constexpr int NF = OP::NF, NR = OP::NR, D3 = OP::D;
+    constexpr int NOWN = T::NOWN, NPOS = T::NPOS, KL = T::KL;
+    constexpr int dZ = T::FY * T::FX, dY = T::FX;  // box strides of the fields
+    constexpr int eZ = T::RY * T::RX, eY = T::RX;  // and of the residuals
+    static_assert(OP::NC == 2 * D3, "consts: the velocities at t - 1, then at t + 1");
+    __shared__ float sF[NF * T::FSZ];
+    __shared__ float sR[NR * T::RSZ];
+    const int t = threadIdx.x;
+    poison_lds(sF, NF * T::FSZ);
+    poison_lds(sR, NR * T::RSZ);
+    if (FPDE_LDS_POISON) __syncthreads();
+
+    // workgroup -> (chunk of levels, block), blocks fastest
+    int lb = remap_xcd(blockIdx.x, D.nblocks);
+    const int gx0 = lb % D.tiles_x * TX;
+    lb /= D.tiles_x;
+    const int gy0 = lb % D.tiles_y * TY;
+    lb /= D.tiles_y;
+    const int tiles_z = (D.nz + TZ - 1) / TZ;
+    const int gz0 = lb % tiles_z * TZ;
+    const int ta = D.lev0 + lb / tiles_z * D.zc, tb = min(ta + D.zc, D.lev0 + D.nlev);
+    const uint32_t vbytes = (uint32_t)D.vol * 4u;
+    const float scale = (float)(two_over_M * (*dloss));
+    auto lv = [&](int l) { return PER ? wrap_idx(l, D.nt) : l; };
+
+    // byte offset of a node in a level; past the range (reads 0) off the grid
+    auto offset = [&](int z, int y, int x) -> uint32_t {
+        if (PER) {
+            z = wrap_idx(z, D.nz);
+            y = wrap_idx(y, D.ny);
+            x = wrap_idx(x, D.nx);
+        } else if (z < 0 || z >= D.nz || y < 0 || y >= D.ny || x < 0 || x >= D.nx) {
+            return kDropOff;
         }
-#pragma unroll
-        for (int f = 0; f < NF; ++f) sc[f] = sn[f];
-        ++L;
+        return (uint32_t)((z * D.ny + y) * D.nx + x) * 4u;
     };
-    float Rm[D3], Rc[D3], Rp[D3];
-    if (PER) {  // from level -1 (= nt - 1): the residual of t0 - 1 is evaluated too
-        L = -1;
-        stars_at_level<OP>(P, D.nt - 1, vbytes, o, n, sc);
-        const int l2 = D.nt - 2;
+    // the field elements this thread brings to LDS
+    uint32_t goff[KL];
 #pragma unroll
-        for (int b = 0; b < D3; ++b) vm[b] = bld(plane_rsrc(P.f[b], l2, vbytes), o);
-        next_R(Rm);
-    } else {  // R(0) = 0; the march starts at level 1 with the velocities of level 0
-        L = 1;
-        stars_at_level<OP>(P, 1, vbytes, o, n, sc);
+    for (int k = 0; k < KL; ++k) {
+        const int i = t + k * NT + T::SKIP, r = i / T::FX;
+        goff[k] = i < T::NLOAD + T::SKIP
+                      ? offset(gz0 + r / T::FY - 2, gy0 + r % T::FY - 2, gx0 + i % T::FX - 2)
+                      : kDropOff;
+    }
+    // the residual positions it evaluates: its own nodes, then nodes of the faces
+    uint32_t at[NPOS], poff[NPOS];  // at: box indices, field | residual << 16
+    uint32_t om = 0, inarr = 0;     // bits: on the spatial residual set; own node on the grid
+#pragma unroll
+    for (int k = 0; k < NPOS; ++k) {
+        int z, y, x;
+        bool have = true;
+        if (k < NOWN) {
+            const int i = t + k * NT;
+            x = i % TX;
+            y = i / TX % TY;
+            z = i / (TX * TY);
+        } else {
+            const int r = t + (k - NOWN) * NT;
+            have = r < T::NFACE;
+            T::face(have ? r : 0, z, y, x);
+        }
+        at[k] = (uint32_t)((z + 2) * dZ + (y + 2) * dY + x + 2) |
+                (uint32_t)((z + 1) * eZ + (y + 1) * eY + x + 1) << 16;
+        const int gz = gz0 + z, gy = gy0 + y, gx = gx0 + x;
+        poff[k] = have ? offset(gz, gy, gx) : kDropOff;
+        const bool set = PER || (gz >= 1 && gz <= D.nz - 2 && gy >= 1 && gy <= D.ny - 2 &&
+                                 gx >= 1 && gx <= D.nx - 2);
+        om |= (uint32_t)(have && set) << k;
+        if (k < NOWN) inarr |= (uint32_t)(gz < D.nz && gy < D.ny && gx < D.nx) << k;
+    }
+
+    float st[NF][KL];  // the next level's fields, on their way to LDS
+    auto load_level = [&](int l) __attribute__((always_inline)) {
+        __amdgpu_buffer_rsrc_t r[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) r[f] = plane_rsrc(P.f[f], lv(l), vbytes);
+#pragma unroll
+        for (int k = 0; k < KL; ++k) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) st[f][k] = bld(r[f], goff[k]);
+        }
+    };
+    auto put_level = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < KL; ++k)
+            if ((k + 1) * NT <= T::NLOAD || t + k * NT < T::NLOAD)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) sF[f * T::FSZ + T::SKIP + k * NT + t] = st[f][k];
+    };
+    // velocities of the levels before and after at the residual positions
+    float vb[NPOS][D3], va[NPOS][D3];
+    auto load_v = [&](int l, float (*v)[D3]) __attribute__((always_inline)) {
 #pragma unroll
         for (int b = 0; b < D3; ++b) {
-            vm[b] = bld(plane_rsrc(P.f[b], 0, vbytes), o);
-            Rm[b] = 0.f;
-        }
-    }
-    next_R(Rc);
-    for (int t = t0; t <= t1; ++t) {
-        next_R(Rp);  // R of level t + 1
-        float tp[D3] = {};
-        OP::add_time(Rm, Rp, K, tp);
+            const __amdgpu_buffer_rsrc_t r = plane_rsrc(P.f[b], lv(l), vbytes);
 #pragma unroll
-        for (int q = 0; q < D3; ++q) {
-            const __amdgpu_buffer_rsrc_t rg = plane_rsrc(P.out[q], t, vbytes);
-            const float g = bld(rg, o);
-            bst<kStream>(rg, o, fmaf(scale, tp[q], g));
-            Rm[q] = Rc[q];
-            Rc[q] = Rp[q];
+            for (int k = 0; k < NPOS; ++k) v[k][b] = bld(r, poff[k]);
+        }
+    };
+    // R at position k (zero off the residual set); vb moves on to this level's velocities
+    auto eval = [&](int k, float* R, float* S) __attribute__((always_inline)) {
+        const float* c = &sF[at[k] & 0xFFFFu];
+        Star s[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f, c += T::FSZ) {
+            s[f].c = c[0];
+            s[f].m[0] = c[-dZ];
+            s[f].p[0] = c[dZ];
+            s[f].m[1] = c[-dY];
+            s[f].p[1] = c[dY];
+            s[f].m[2] = c[-1];
+            s[f].p[2] = c[1];
+        }
+        float cc[2 * D3];
+#pragma unroll
+        for (int b = 0; b < D3; ++b) {
+            cc[b] = vb[k][b];
+            cc[D3 + b] = va[k][b];
+            vb[k][b] = s[b].c;
+        }
+        OP::residual(s, cc, K, R);
+#pragma unroll
+        for (int b = 0; b < NR; ++b) R[b] = om >> k & 1u ? R[b] : 0.f;
+        if (S) OP::gather_self(s, R, K, S);
+    };
+
+    // levels whose residuals are evaluated: those of the chunk and one more at each
+    // end, except the end levels of the grid, which hold none
+    const int l0 = PER || ta >= 2 ? ta - 1 : ta, l1 = PER || tb <= D.nt - 2 ? tb : tb - 1;
+    float Rb[NOWN][D3], Rbb[NOWN][D3], G[NOWN][D3];  // R of t - 1, t - 2; gradient of t - 1
+#pragma unroll
+    for (int k = 0; k < NOWN; ++k)
+#pragma unroll
+        for (int q = 0; q < D3; ++q) Rb[k][q] = Rbb[k][q] = G[k][q] = 0.f;
+    double acc = 0.0;
+    // adds the time part to level l - 1's gradient and writes it, R: the residual of level l
+    auto finish = [&](int l, int k, const float* R) __attribute__((always_inline)) {
+        float tp[D3] = {};
+        OP::add_time(Rbb[k], R, K, tp);
+        const uint32_t so = inarr >> k & 1u ? poff[k] : kDropOff;
+#pragma unroll
+        for (int q = 0; q < D3; ++q)
+            bst<kStream>(plane_rsrc(P.out[q], l - 1, vbytes), so, fmaf(scale, tp[q], G[k][q]));
+    };
+    load_level(l0);
+    load_v(l0 - 1, vb);
+    load_v(l0 + 1, va);
+    put_level();
+    __syncthreads();
+#pragma unroll 1
+    for (int l = l0; l <= l1; ++l) {  // sF: the fields of level l
+        const bool full = l >= ta && l < tb;
+        float R[NOWN][NR], S[NOWN][D3];
+#pragma unroll
+        for (int k = 0; k < NOWN; ++k) {
+            eval(k, R[k], S[k]);
+            if (full) {
+#pragma unroll
+                for (int b = 0; b < NR; ++b) sR[b * T::RSZ + (at[k] >> 16)] = R[k][b];
+                if (LOSS) {
+                    float ss = 0.f;
+#pragma unroll
+                    for (int b = 0; b < NR; ++b) ss = fmaf(R[k][b], R[k][b], ss);
+                    acc += (double)(inarr >> k & 1u ? ss : 0.f);
+                }
+            }
+            if (l > ta) finish(l, k, R[k]);
+#pragma unroll
+            for (int q = 0; q < D3; ++q) {
+                Rbb[k][q] = Rb[k][q];
+                Rb[k][q] = R[k][q];
+            }
+        }
+#pragma unroll
+        for (int k = NOWN; k < NPOS; ++k) {
+            if ((k - NOWN + 1) * NT <= T::NFACE || t + (k - NOWN) * NT < T::NFACE) {
+                float Rr[NR];
+                eval(k, Rr, nullptr);
+                if (full)
+#pragma unroll
+                    for (int b = 0; b < NR; ++b) sR[b * T::RSZ + (at[k] >> 16)] = Rr[b];
+            }
+        }
+        if (l < l1) {
+            load_level(l + 1);
+            load_v(l + 2, va);
+        }
+        __syncthreads();
+        if (full) {
+#pragma unroll
+            for (int k = 0; k < NOWN; ++k) {
+                Star fs[NF] = {}, rs[NR];
+                const float* c = &sF[at[k] & 0xFFFFu];
+#pragma unroll
+                for (int f = 0; f < D3; ++f, c += T::FSZ) {
+                    fs[f].m[0] = c[-dZ];
+                    fs[f].p[0] = c[dZ];
+                    fs[f].m[1] = c[-dY];
+                    fs[f].p[1] = c[dY];
+                    fs[f].m[2] = c[-1];
+                    fs[f].p[2] = c[1];
+                }
+                const float* e = &sR[at[k] >> 16];
+#pragma unroll
+                for (int b = 0; b < NR; ++b, e += T::RSZ) {
+                    rs[b].c = R[k][b];
+                    rs[b].m[0] = e[-eZ];
+                    rs[b].p[0] = e[eZ];
+                    rs[b].m[1] = e[-eY];
+                    rs[b].p[1] = e[eY];
+                    rs[b].m[2] = e[-1];
+                    rs[b].p[2] = e[1];
+                }
+                float g[NF];
+                OP::gather_rest(fs, rs, S[k], K, g);
+                bst<kStream>(plane_rsrc(P.out[D3], l, vbytes),
+                             inarr >> k & 1u ? poff[k] : kDropOff, scale * g[D3]);
+#pragma unroll
+                for (int q = 0; q < D3; ++q) G[k][q] = scale * g[q];
+            }
+            __syncthreads();
+        }
+        if (l < l1) {
+            put_level();
+            __syncthreads();
         }
     }
+    if (l1 < tb) {  // the level after the chunk is the grid's last: R = 0 there
+#pragma unroll
+        for (int k = 0; k < NOWN; ++k) {
+            const float R[NR] = {};
+            finish(tb, k, R);
+        }
+    }
+    if (LOSS) block_loss<NT>(acc * inv_M, loss, ws);
 }
 
 // Boundary-gradient correction on a 3D+t grid: the end time levels t = 0 and

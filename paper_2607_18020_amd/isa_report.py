@@ -26,8 +26,8 @@ from typing import Dict, List
 
 from paper_2607_18020_amd.csrc import build as B
 
-KERNEL_PREFIXES = ("fwd_kernel", "fwdq_kernel", "bwd_kernel", "bwdq_kernel", "vjp_kernel", "bc_kernel",
-                   "bc4_kernel", "tm_kernel", "zero_levels_kernel", "fill_f64_kernel")
+KERNEL_PREFIXES = ("fwd_kernel", "fwdq_kernel", "bwd_kernel", "bwdq_kernel", "bwdt_kernel", "vjp_kernel", "bc_kernel",
+                   "bc4_kernel", "zero_levels_kernel", "fill_f64_kernel")
 
 
 def compile_asm(path: str) -> None:
@@ -161,11 +161,13 @@ def _template_args(name: str) -> List[str]:
 def reduces_loss(name: str) -> bool:
     """The kernels that add a float64 partial loss per workgroup: every forward,
     and the backwards with their LOSS flag (bwd_kernel<OP, TX, TY, REV, LOSS, PER>,
-    bwdq_kernel<OP, NW, Q, LOSS, PER>)."""
+    bwdq_kernel<OP, NW, Q, LOSS, PER>, bwdt_kernel<OP, TZ, TY, TX, NT, LOSS, PER>)."""
     if name.startswith(("fwd_kernel", "fwdq_kernel")):
         return True
     if name.startswith("bwdq_kernel"):
         return _template_args(name)[3] == "true"
+    if name.startswith("bwdt_kernel"):
+        return _template_args(name)[5] == "true"
     return name.startswith("bwd_kernel") and _template_args(name)[4] == "true"
 
 

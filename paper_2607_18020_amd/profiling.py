@@ -34,7 +34,7 @@ STREAM_KERNEL = "MulFunctor"  # the benchmark's 1 GiB y = 1 * x kernel
 STREAM_BYTES = 1 << 30
 # the library's kernels (name stems)
 KERNELS = ("fwd_kernel", "fwdq_kernel", "bwd_kernel", "bwdq_kernel", "bc_kernel", "bc4_kernel", "vjp_kernel",
-           "tm_kernel", "zero_levels_kernel", "fill_f64")
+           "bwdt_kernel", "zero_levels_kernel", "fill_f64")
 
 
 def _code_only(text: str) -> str:

@@ -23,7 +23,12 @@ CASES = [
     (W.HEAT_3D_BE, (20, 41, 255)),   # wide ones
     (W.POISSON_3D, (70, 12, 257)),
     (W.NS_3DT, (4, 19, 13, 131)),
+    # the time-marching backward's blocks: 4x8x32 (one chunk of levels per level, and
+    # two chunks), 8x6x32 and 8x8x32, ragged against each
     (W.NS_3DT, (5, 9, 21, 33)),
+    (W.NS_3DT, (12, 21, 47, 90)),
+    (W.NS_3DT, (5, 17, 41, 65)),
+    (W.NS_3DT, (5, 64, 57, 123)),
 ]
 
 
