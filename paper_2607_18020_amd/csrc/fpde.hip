@@ -5,7 +5,6 @@
 #include <stdint.h>
 #include <string.h>
 
-#include <algorithm>
 #include <tuple>
 #include <type_traits>
 
@@ -389,8 +388,8 @@ Dims tile_dims(const Dims& n, int TX, int TY, int zc) {
 // workgroups per CU a step of an LDS march costs 0.3 + 0.7 k / RES of a full
 // round's, the fullest CU deciding (NS-3D, two per CU: 0.65 at one; heat 97 x 90 x 41
 // backward 6.3 us in 228 workgroups, 7.2 in 288); one of a register-queue march,
-// whose waves wait for nobody, max(0.25 + 0.75 / RES, 0.1 + 0.9 k / RES), its
-// latency or its throughput (2-D backward, eight per CU, us per row at 1, 2, 3.8,
+// whose waves wait for nobody, 1 / RES + (1 - 1 / RES) k / RES, its
+// latency and then its throughput (2-D backward, eight per CU, us per row at 1, 2, 3.8,
 // 6.5 and 8: 0.22, 0.26, 0.40, 0.66, 0.8).
 // A loss costs one atomic per workgroup of the last round, serialised at 12 ns,
 // about 0.015 of a step, or through a workspace a second level of slots beyond 64
@@ -426,8 +425,7 @@ Chunks plan_chunks(const Dims& n, int TX, int TY, int res, Sum sum, double prolo
         const long long round = (long long)kCUs * res, full = W / round;
         const long long rest = W - full * round;
         const double k = queue ? (double)rest / kCUs : (double)((rest + kCUs - 1) / kCUs);
-        const double last = queue ? std::max(0.25 + 0.75 / res, 0.1 + 0.9 * k / res)
-                                  : 0.3 + 0.7 * k / res;
+        const double last = queue ? 1.0 / res + (1.0 - 1.0 / res) * k / res : 0.3 + 0.7 * k / res;
         double cost = (zc + prologue) * ((double)full + (rest ? last : 0.0));
         if (sum == Sum::atomics) cost += 0.015 * (double)(W < round ? W : round);
         if (sum == Sum::workspace && W > kGroup) cost += 0.8;
