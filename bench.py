@@ -293,8 +293,9 @@ def copy_gbps(torch, nbytes=1 << 30, reps=20):
     return 2 * nbytes / s / 1e9
 
 
-# the kernels one timed call queues, where it queues several
-TRAFFIC_KERNELS = {"value_and_grad": ("fill_f64", "bwd")}
+# the kernels one timed call queues, where they are not named like it (bound
+# calls: no loss fill)
+TRAFFIC_KERNELS = {"value_and_grad": ("bwd",)}
 OP_KERNEL_TAG = {1: "OpBurgers", 2: "OpHelmholtz", 3: "OpHeat", 4: "OpNS<2, false>",
                  5: "OpNS<3, true>", 6: "OpNS<3, false>", 7: "OpPoisson<2>", 8: "OpPoisson<3>",
                  9: "OpNST", 10: "OpNS3T"}
@@ -317,8 +318,10 @@ def measured_traffic(cfg, op, kernels, path="loss"):
         return None
     total = 0.0
     for stem in kernels:
-        prefix = stem if stem.startswith("fill") else f"{stem}_kernel<{OP_KERNEL_TAG[op]}"
-        hits = [v for name, v in rec.get("kernels", {}).items() if name.startswith(prefix)]
+        # (2-D grids: fwdq_kernel, bwdq_kernel; the 3D+t backward: bwdt_kernel)
+        prefixes = (stem,) if stem.startswith("fill") else tuple(
+            f"{stem}{v}_kernel<{OP_KERNEL_TAG[op]}" for v in ("", "q", "t"))
+        hits = [v for name, v in rec.get("kernels", {}).items() if name.startswith(prefixes)]
         if len(hits) != 1:
             return None
         total += hits[0]["fetch_bytes"] + hits[0]["write_bytes"]

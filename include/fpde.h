@@ -242,14 +242,13 @@ int fpde_residual_vjp(int op, const fpde_grid* grid, const fpde_coeffs* coeffs,
  *   - fpde_residual_fwd4 queues the loss fill and one march over every interior
  *     time level; with residual_out, also a fill of zeros on the end levels
  *     (3 kernels);
- *   - fpde_residual_bwd4 writes every node of the levels 1 .. n[0] - 2 with two
- *     kernels: a march over each level (the spatial part of the transposed
- *     stencil, boundary nodes of the level included), then a march along the
- *     time axis that adds the time part (R_q(t-1) - R_q(t+1)) / (2 h_t) at every
- *     node of the spatial residual set, recomputing those residuals;
+ *   - fpde_residual_bwd4 writes every node of the levels 1 .. n[0] - 2 (boundary
+ *     nodes of the level included) with one kernel, a march along the time axis:
+ *     the spatial part of the transposed stencil plus the time part
+ *     (R_q(t-1) - R_q(t+1)) / (2 h_t);
  *   - fpde_bc_correct4 writes the end levels 0 and n[0] - 1 (1 kernel);
- *   - fpde_residual_value_and_grad4 queues the fill, the level march with the
- *     loss, the time march and (bc_mode 0) the end-level kernel;
+ *   - fpde_residual_value_and_grad4 queues the fill, the time march with the
+ *     loss and (bc_mode 0) the end-level kernel;
  *   - fpde_residual_vjp4 queues one march over every level; the time part comes
  *     from the sensitivities of the neighbouring levels at the node itself.
  * Queues nothing and returns an error status on invalid arguments, as above. */

@@ -196,9 +196,13 @@ def _used_on(stream, *tensors):
             t.record_stream(stream)
 
 
-def _loss_workspace(stream, dev) -> torch.Tensor:
-    """A zeroed loss workspace, allocated and zeroed on the stream whose calls use it."""
+def _loss_workspace(stream, dev) -> Optional[torch.Tensor]:
+    """A zeroed loss workspace, allocated and zeroed on the stream whose calls use
+    it; None while that stream is being captured (the zeroing would be part of
+    the graph, and not done for calls outside it)."""
     with torch.cuda.stream(stream):  # (None: the current stream)
+        if torch.cuda.is_current_stream_capturing():
+            return None
         return torch.zeros(WORKSPACE_BYTES // 8, dtype=torch.float64, device=dev)
 
 
@@ -354,6 +358,8 @@ def bind(entry: str, op: int, fields, consts, h, coeffs, *, dloss=None, grads=No
             raise ValueError(f"bind {entry}: loss must be a one-element float64 tensor on the "
                              "fields' device")
         ws = _loss_workspace(stream, dev)
+        wa = () if ws is None else (ws.data_ptr(),)
+        sfx = "4" if ws is None else "_ws4"
         keep += [loss, ws]
     if entry == "fwd":
         ra = None
@@ -361,9 +367,9 @@ def bind(entry: str, op: int, fields, consts, h, coeffs, *, dloss=None, grads=No
             _check_tensors(residual_out, shape, "bind fwd residual_out")
             ra = _ptr_array(residual_out)
             keep += [ra, list(residual_out)]
-        args = (int(op), ctypes.byref(g), ctypes.byref(c), fa, ca, ra, loss.data_ptr(),
-                ws.data_ptr(), sh)
-        return BoundCall("fpde_residual_fwd", lib.fpde_residual_fwd_ws4, args, keep, loss)
+        args = (int(op), ctypes.byref(g), ctypes.byref(c), fa, ca, ra, loss.data_ptr(), *wa, sh)
+        return BoundCall("fpde_residual_fwd", getattr(lib, "fpde_residual_fwd" + sfx), args, keep,
+                         loss)
     if grads is None:
         grads = [torch.empty_like(f) for f in fields]
         _used_on(stream, *grads)
@@ -386,9 +392,10 @@ def bind(entry: str, op: int, fields, consts, h, coeffs, *, dloss=None, grads=No
     keep.append(dloss)
     if entry == "value_and_grad":
         args = (int(op), ctypes.byref(g), ctypes.byref(c), fa, ca, dloss.data_ptr(),
-                loss.data_ptr(), ga, ws.data_ptr(), sh)
-        return BoundCall("fpde_residual_value_and_grad", lib.fpde_residual_value_and_grad_ws4,
-                         args, keep, (loss, grads))
+                loss.data_ptr(), ga, *wa, sh)
+        return BoundCall("fpde_residual_value_and_grad",
+                         getattr(lib, "fpde_residual_value_and_grad" + sfx), args, keep,
+                         (loss, grads))
     if entry not in ("bwd", "bc"):
         raise ValueError(f"bind: unknown entry point {entry!r}")
     name = "fpde_residual_bwd" if entry == "bwd" else "fpde_bc_correct"

@@ -6,8 +6,9 @@
 // row segment) and marches a chunk of planes along axis 0.  Each plane region
 // streams from memory straight into a ring of LDS slots, so every input element
 // is read from HBM once per chunk plus the halo; the 7-point star of a node is
-// read from the slots of planes z-1, z, z+1.  (The register-queue forward,
-// fwdq_kernel, keeps its planes in per-lane registers instead.)
+// read from the slots of planes z-1, z, z+1.  (The register-queue kernels of the
+// 2-D grids, fwdq_kernel and bwdq_kernel, keep their rows in per-lane registers
+// instead; the 3D+t backward, bwdt_kernel, marches time over blocks of nodes.)
 //
 // Forward: one residual per interior node, sum of squares accumulated in a
 // per-thread float64 register, reduced with DPP across the wavefront and through
@@ -817,7 +818,7 @@ __global__ __launch_bounds__(TX* TY) void fwdq_kernel(Ptrs P, Dims D, KCoef K, d
 // Waves per SIMD asked for: 512-thread tiles of several fields run two to a CU
 // (their LDS allows it), which needs four waves of at most 128 VGPRs per SIMD.
 template <class OP, int NT>
-constexpr int kBwdMinW = (OP::NF > 1 && OP::DIM == 3 && !OP::TIME && NT == 512) ? 4 : FPDE_BWD_MINW;
+constexpr int kBwdMinW = (OP::NF > 1 && OP::DIM == 3 && NT == 512) ? 4 : FPDE_BWD_MINW;
 
 template <class OP, int TX, int TY, bool REV, bool LOSS, bool PER>
 __global__ __launch_bounds__(TX* TY, (kBwdMinW<OP, TX * TY>)) void bwd_kernel(Ptrs P, Dims D, KCoef K,
@@ -832,6 +833,7 @@ __global__ __launch_bounds__(TX* TY, (kBwdMinW<OP, TX * TY>)) void bwd_kernel(Pt
     constexpr int RHY = (DIM == 3) ? 1 : 0;  // R-tile halo (y)
     constexpr int RLY = TY + 2 * RHY, RLX = TX + 2;
     using PS = PlaneStream<FLY * FLX, NT>;
+    static_assert(!OP::TIME, "3D+t grids: bwdt_kernel");
     static_assert(DIM == 3 || TY == 1, "2-D grids use one-row tiles");
     static_assert(Ring<TX, TY, DIM>::COUNT <= NT, "ring larger than the workgroup");
     // The chunk [z0, z1) of axis 0 is marched in steps w = 0 .. L-1 over the
@@ -847,7 +849,6 @@ __global__ __launch_bounds__(TX* TY, (kBwdMinW<OP, TX * TY>)) void bwd_kernel(Pt
     poison_lds(&sR[0][0][0], (int)(sizeof(sR) / 4));
     if (FPDE_LDS_POISON) __syncthreads();
     const TileCoord tc = tile_coord<TX, TY>(D);
-    time_level<OP>(P, D, tc.lev);
     const int z0 = tc.z0, z1 = tc.z1, L = z1 - z0;
     auto ph = [&](int w) {  // (wrapped into the grid when periodic)
         const int p = REV ? z1 - 1 - w : z0 + w;
@@ -1804,7 +1805,7 @@ __global__ __launch_bounds__(NT) void bwdt_kernel(Ptrs P, Dims D, KCoef K, const
 }
 
 // Boundary-gradient correction on a 3D+t grid: the end time levels t = 0 and
-// t = nt - 1 (the end planes of array axis 0), which the level marches do not
+// t = nt - 1 (the end planes of array axis 0), which the time march does not
 // visit.  A node whose only boundary coordinate is t receives the time term of
 // its inward neighbour's residuals (level 1 or nt - 2); a node on the spatial
 // boundary as well touches no residual node and gets 0.  One workgroup per 256

@@ -380,14 +380,14 @@ struct OpNST {
 // on array axis b + 1, pressure last.
 //   R_b = D1_t c_b + sum_a c_a D1_a c_b + D1_b p - nu lap c_b      (a, b over x, y, z)
 //   R_div = sum_a D1_a c_a
-// The kernels run the 3-D engine on one time level t at a time (TIME): the
+// The kernels evaluate one time level t at a time (TIME): the
 // stars here are spatial (index a = spatial axis a, array axis a + 1) and the
 // velocities at the neighbouring time levels enter as point values, the consts
 // c[0..2] = c_b(t - 1) and c[3..5] = c_b(t + 1) (TSRC / TOFF: the field and
 // the time offset each const is read from).  The gather below is the spatial
 // part of the transposed stencil; its time part, (R_q(t-1) - R_q(t+1)) / (2 h_t),
-// needs the residuals of other time levels and is added by the time-march
-// kernel (or, from given sensitivities, by the explicit-sensitivity backward).
+// needs the residuals of other time levels: add_time adds it, in the
+// time-marching backward or (from given sensitivities) the explicit-sensitivity one.
 struct OpNS3T {
     static constexpr int D = 3;  // spatial dimensions
     static constexpr int DIM = 3, NF = D + 1, NC = 2 * D, NR = D + 1, NG = D, NFG = D;

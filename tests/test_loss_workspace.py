@@ -100,13 +100,27 @@ def test_bound_calls_on_two_streams_and_captured():
     torch.cuda.synchronize()
     for call, ref in zip(calls, refs):
         assert abs(call.result.item() - ref) <= 1e-12 * ref
-    # captured: no reference to the workspace, and every replay starts from zero
+    # captured: no reference to the workspace, and every replay starts from zero;
+    # a call bound while capturing works outside the graph too
     g = torch.cuda.CUDAGraph()
     loss = torch.empty((), dtype=torch.float64, device="cuda")
-    with torch.cuda.graph(g):
-        B.bind("fwd", op, f, [], h, co, loss=loss)()
+    loss2 = torch.empty((), dtype=torch.float64, device="cuda")
+    before = B.bind("fwd", op, f, [], h, co, loss=loss2, stream=streams[0])
+    with torch.cuda.graph(g, stream=streams[0]):
+        inside = B.bind("fwd", op, f, [], h, co, loss=loss)
+        inside()
+        before()
     for _ in range(3):
+        loss.fill_(float("nan"))
+        loss2.fill_(float("nan"))
         g.replay()
         calls[1]()
         torch.cuda.synchronize()
         assert abs(loss.item() - refs[1]) <= 1e-12 * refs[1]
+        assert abs(loss2.item() - refs[1]) <= 1e-12 * refs[1]
+    for call in (inside, before):
+        call.result.fill_(float("nan"))
+        torch.cuda.synchronize()
+        call()
+        torch.cuda.synchronize()
+        assert abs(call.result.item() - refs[1]) <= 1e-12 * refs[1]
