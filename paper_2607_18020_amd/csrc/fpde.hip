@@ -142,18 +142,23 @@ struct Geo3 {
 // narrow one on short rows and small grids (374 x 447: 7.9 and 7.0 us; Burgers
 // 128 x 256: 5.9 and 4.7, 5.5 of each the launches), and with a workspace
 // (Helmholtz 1024^2: 8.0 and 7.4).
-template <int RF, int RF2, int RB>
+// RBA waves per workgroup where the value and gradient sums its loss by atomics: one
+// field's workgroups finish together, and half as many of eight waves wait for half
+// the atomics (Helmholtz 2048^2 19.4 -> 17.7 us, 901 x 480 9.1 -> 8.4, Burgers
+// 1397 x 1661 13.8 -> 11.7); three fields are no faster so (2048^2 26.7 -> 28.0).
+template <int RF, int RF2, int RB, int RBA>
 struct Geo2 {
     static constexpr bool D3 = false;
     static constexpr double PROLOGUE = 5.0;
     using TF = Tile<FPDE_TX2_FWD, 1, RF>;
     using TF2 = Tile<256, 1, RF2, 98>;
     using TB = Tile<62 * FPDE_BWD2_NW, 1, RB>;
+    using TBA = Tile<62 * RBA, 1, RB * FPDE_BWD2_NW / RBA>;
     using TV = Tile<FPDE_TX2, 1, 4>;
     using TV2 = TV;
 };
-using Geo2One = Geo2<2, 8, 8>;  // one field: up to 64 VGPRs (the value and gradient 78)
-using Geo2NS = Geo2<1, 4, 3>;   // three: 120, backward 152
+using Geo2One = Geo2<2, 8, 8, 8>;  // one field: up to 64 VGPRs (the value and gradient 78)
+using Geo2NS = Geo2<1, 4, 3, FPDE_BWD2_NW>;   // three: 120, backward 152
 // several fields with nonlinear coupling (NS): two 512-thread forward workgroups
 // per CU (57 KB of LDS each), one 1024-thread backward (148 KB) or two 512-thread
 // ones (79 KB), two 256-thread explicit-sensitivity ones (57 KB).  The narrow
@@ -547,9 +552,8 @@ int launch_bwd(const Req& r, const double* dloss, int zc, double* loss) {
 }
 
 // 2-D register-queue backward (with the loss when given)
-template <class OP>
+template <class OP, int NW>
 int launch_bwdq(const Req& r, const double* dloss, int zc, double* loss) {
-    constexpr int NW = FPDE_BWD2_NW;
     const Dims dm = tile_dims(r.dims, 62 * NW, 1, zc);
     double* ws = nullptr;
     int st = loss ? begin_loss(r, dm.nblocks, loss, &ws) : FPDE_OK;
@@ -615,11 +619,15 @@ int launch_fwd2(const Req& r, bool store, double* loss) {
 }
 template <class GEO, class OP>
 int launch_bwd2(const Req& r, const double* dloss, double* loss) {
-    using T = typename GEO::TB;
     if constexpr (FPDE_BWD2_QUEUE) {
-        const int zc =
-            plan_chunks(r.dims, T::TX, 1, T::RES, loss_sum(r, loss), GEO::PROLOGUE, true).zc;
-        return launch_bwdq<OP>(r, dloss, zc, loss);
+        auto run = [&](auto t) {
+            using T = decltype(t);
+            const int zc =
+                plan_chunks(r.dims, T::TX, 1, T::RES, loss_sum(r, loss), GEO::PROLOGUE, true).zc;
+            return launch_bwdq<OP, T::TX / 62>(r, dloss, zc, loss);
+        };
+        if (loss_sum(r, loss) == Sum::atomics) return run(typename GEO::TBA{});
+        return run(typename GEO::TB{});
     } else {
         const int zc = plan_chunks(r.dims, FPDE_TX2, 1, 4, loss_sum(r, loss), kPrologue).zc;
         return launch_bwd<OP, FPDE_TX2, 1>(r, dloss, zc, loss);

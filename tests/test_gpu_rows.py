@@ -1,5 +1,5 @@
 """2-D launches at the edges of their row segments and chunks: rows of one wave's
-62 output columns and one more, the 248-column backward and the 256- and 1024-node
+62 output columns and one more, the 248- and 496-column backwards and the 256- and 1024-node
 forward segments and one more, two and three interior rows, chunk ends.  Every
 entry point against the oracle, node by node, in both boundary modes; the one-pass
 gradient bitwise bwd + bc on the rows both march."""
@@ -13,7 +13,7 @@ from tests import gpu_helpers as H
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(3, 3), (4, 62), (5, 64), (3, 248), (9, 249), (40, 256), (33, 257), (130, 65),
+SHAPES = [(3, 3), (4, 62), (5, 64), (3, 248), (9, 249), (40, 256), (33, 257), (130, 65), (12, 497),
           (21, 1025), (600, 6)]
 
 
