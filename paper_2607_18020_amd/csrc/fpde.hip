@@ -678,14 +678,17 @@ int launch_bwdt(const Req& r, const double* dloss, double* loss, std::tuple<T...
     Dims q = {};  // a launch's chunks: those of a march over nlev planes of its blocks
     q.ny = q.nlev = 1;
     q.nz = r.dims.nlev;
-    int best = 0, zc = 0, i = 0;
+    int best = -1, zc = 0, i = 0;
     double cost = 0.0;
     auto consider = [&](auto t) {
         using B = decltype(t);
         q.nx = ((r.dims.nx + B::TX - 1) / B::TX) * ((r.dims.ny + B::TY - 1) / B::TY) *
                ((r.dims.nz + B::TZ - 1) / B::TZ);
         const Chunks c = plan_chunks(q, 1, 1, 1, loss_sum(r, loss), 2.0);
-        if (i == 0 || c.cost * B::STEP < cost) {
+        // (a launch holds fewer than 2^32 threads: on a level a few nodes thin, where a
+        // block is mostly empty, the blocks with more threads per node are out; the
+        // 8 x 8 x 32 ones, half a thread each, fit every level)
+        if ((long long)q.nx * B::NT < (1LL << 32) && (best < 0 || c.cost * B::STEP < cost)) {
             best = i;
             zc = c.zc;
             cost = c.cost * B::STEP;
@@ -693,7 +696,7 @@ int launch_bwdt(const Req& r, const double* dloss, double* loss, std::tuple<T...
         ++i;
     };
     (consider(T{}), ...);
-    int st = FPDE_OK;
+    int st = FPDE_ERR_HIP;  // (the runtime would refuse every one of them)
     i = 0;
     ((i++ == best ? (void)(st = launch_bwdt_as<OP, T>(r, dloss, loss, zc)) : (void)0), ...);
     return st;

@@ -1,0 +1,32 @@
+"""The launch rule on the host (no GPU): what each call would queue, read from the
+library's own host source (tests/c/launch_rule.cpp)."""
+from __future__ import annotations
+
+import os
+
+import pytest
+
+from paper_2607_18020_amd import workloads as W
+from paper_2607_18020_amd.csrc import build as B
+from tests import launch_rule as L
+
+pytestmark = pytest.mark.skipif(not os.path.exists(B.HIPCC), reason="hipcc not available")
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    return L.compile_rule(tmp_path_factory.mktemp("rule"))
+
+
+# long thin space-time levels: few nodes per block of the time march
+@pytest.mark.parametrize("call", ["bwd", "vg"])
+@pytest.mark.parametrize("shape", [(3, 50_000_000, 3, 3), (3, 25_000_000, 7, 3),
+                                   (4, 19_000_000, 9, 3), (3, 3, 3, 50_000_000)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_time_march_stays_launchable(rule, call, shape):
+    """A launch holds fewer than 2^32 threads (the runtime refuses more), for every
+    level that the size limits admit."""
+    for ls in L.launches(rule, [(call, W.NS_3DT, shape, bc) for bc in (0, 1)]):
+        assert "bwdt_kernel" in [x.name for x in ls]
+        for x in ls:
+            assert x.blocks * x.threads < 1 << 32, x
