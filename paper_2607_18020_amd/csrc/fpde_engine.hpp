@@ -1707,9 +1707,13 @@ __global__ __launch_bounds__(NT) void bwdt_kernel(Ptrs P, Dims D, KCoef K, const
         float tp[D3] = {};
         OP::add_time(Rbb[k], R, K, tp);
         const uint32_t so = inarr >> k & 1u ? poff[k] : kDropOff;
+        // (off the residual set there is no time part: with a scale that is not finite,
+        // its product with 0 would turn an infinite gradient into NaN)
+        const bool set = om >> k & 1u;
 #pragma unroll
         for (int q = 0; q < D3; ++q)
-            bst<kStream>(plane_rsrc(P.out[q], l - 1, vbytes), so, fmaf(scale, tp[q], G[k][q]));
+            bst<kStream>(plane_rsrc(P.out[q], l - 1, vbytes), so,
+                         set ? fmaf(scale, tp[q], G[k][q]) : G[k][q]);
     };
     load_level(l0);
     load_v(l0 - 1, vb);

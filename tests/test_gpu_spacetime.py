@@ -117,3 +117,29 @@ def test_deterministic_and_accumulate():
     torch.cuda.synchronize()
     for a, i, o in zip(acc, init, over):
         assert torch.equal(a, i + o)
+
+
+@pytest.mark.parametrize("bc_mode", [0, 1])
+def test_infinite_upstream_derivative(bc_mode):
+    """dloss = inf (an overflowed loss scale): a node off the spatial residual set has
+    a spatial part only, so its gradient is inf times the unscaled one (inf * 0 = NaN
+    where that is zero); everywhere else no node is finite."""
+    import torch  # noqa: PLC0415
+    from paper_2607_18020_amd import binding as B  # noqa: PLC0415
+    wl = W.make("ns_3dt", seed=43, shape=(6, 9, 13, 37))
+    f = _dev(wl.fields)
+    one = B.fpde_residual_bwd(wl.op, f, [], wl.h, wl.coeffs, 1.0, bc_mode=bc_mode)
+    big = B.fpde_residual_bwd(wl.op, f, [], wl.h, wl.coeffs, float("inf"), bc_mode=bc_mode)
+    _, vg = B.fpde_residual_value_and_grad(wl.op, f, [], wl.h, wl.coeffs, float("inf"),
+                                           bc_mode=bc_mode)
+    torch.cuda.synchronize()
+    edge = np.ones(wl.shape[1:], bool)
+    edge[1:-1, 1:-1, 1:-1] = False
+    levels = slice(None) if bc_mode else slice(1, -1)
+    for a, b, v in zip(one, big, vg):
+        a, b, v = (x.cpu().numpy()[levels] for x in (a, b, v))
+        assert not np.isfinite(b).any() and np.array_equal(b, v, equal_nan=True)
+        if bc_mode == 0:
+            with np.errstate(invalid="ignore"):
+                assert np.array_equal(b[:, edge], np.float32(np.inf) * a[:, edge], equal_nan=True)
+            assert np.isinf(b[:, edge]).any()
