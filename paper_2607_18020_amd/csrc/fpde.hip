@@ -558,13 +558,15 @@ int launch_bwdq(const Req& r, const double* dloss, int zc, double* loss) {
     double* ws = nullptr;
     int st = loss ? begin_loss(r, dm.nblocks, loss, &ws) : FPDE_OK;
     if (st != FPDE_OK) return st;
-    with_flag(loss != nullptr, [&](auto lo) {
+    auto go = [&](auto lo) {
         with_flag(dm.per, [&](auto per) {
             st = launch(bwdq_kernel<OP, NW, FPDE_BWD2_Q, decltype(lo)::value, decltype(per)::value>,
                         dim3(dm.nblocks), dim3(64 * NW), r.stream, r.P, dm, r.K, dloss,
                         r.two_over_M, r.inv_M, loss, ws);
         });
-    });
+    };
+    if constexpr (NW == FPDE_BWD2_NW) with_flag(loss != nullptr, go);
+    else go(std::true_type{});  // (the other widths are taken with a loss only)
     return st;
 }
 

@@ -5,10 +5,11 @@
  * GPU (compiled for the host only: no device code).  One request per line of
  * standard input:
  *     call op bc_mode ndim n0 [n1 [n2 [n3]]]
- * with call one of fwd, fwdR (residuals stored), fwd_ws, bwd, vg, vg_ws, bc, vjp.
+ * with call one of fwd, fwdR (residuals stored), fwd_ws, bwd, vg, vg_ws, bc, vjp, vjp_acc.
  * One answer per launch,
  *     <device kernel name> <workgroups> <threads> [<chunk length> <tiles_x> <tiles_y>]
- * (the bracket for the marching kernels), then "= <status>".
+ * (the bracket for the marching kernels), then "= <status>".  With an argument: the
+ * names of the library's kernels instead.
  */
 #include "fpde.hip"
 
@@ -44,7 +45,11 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
 }
 }
 
-int main() {
+int main(int argc, char**) {
+    if (argc > 1) {
+        for (const auto& k : g_names) printf("%s\n", k.second.c_str());
+        return 0;
+    }
     // device addresses far apart, never dereferenced
     const float *f[4], *c[6], *s[4];
     float* o[4];
@@ -77,6 +82,7 @@ int main() {
         if (w == "bwd") st = fpde_residual_bwd4(op, &g, &co, f, c, dl, o, nullptr);
         if (w == "bc") st = fpde_bc_correct4(op, &g, &co, f, c, dl, o, nullptr);
         if (w == "vjp") st = fpde_residual_vjp4(op, &g, &co, f, s, 0, o, nullptr);
+        if (w == "vjp_acc") st = fpde_residual_vjp4(op, &g, &co, f, s, 1, o, nullptr);
         if (w == "vg")
             st = fpde_residual_value_and_grad4(op, &g, &co, f, c, dl, loss, o, nullptr);
         if (w == "vg_ws")

@@ -50,16 +50,26 @@ def compile_rule(out_dir, extra=()) -> str:
     return exe
 
 
+def _plain(names):
+    r = subprocess.run(["c++filt"], input="\n".join(names), capture_output=True, text=True,
+                       check=True)
+    return {m: d.replace("fpde::", "").split("(")[0].replace("void ", "")
+            for m, d in zip(names, r.stdout.splitlines())}
+
+
+def kernels(exe: str) -> set:
+    """Every kernel of the library."""
+    names = subprocess.run([exe, "kernels"], capture_output=True, text=True, check=True).stdout
+    return set(_plain(names.split()).values())
+
+
 def launches(exe: str, requests) -> List[List[Launch]]:
     """For each (call, op, shape, bc_mode): its launches.  Every call must succeed."""
     text = "".join(f"{call} {op} {bc} {len(shape)} {' '.join(map(str, shape))}\n"
                    for call, op, shape, bc in requests)
     out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
     names = sorted({ln.split()[0] for ln in out.splitlines() if ln.startswith("_Z")})
-    r = subprocess.run(["c++filt"], input="\n".join(names), capture_output=True, text=True,
-                       check=True)
-    plain = {m: d.replace("fpde::", "").split("(")[0].replace("void ", "")
-             for m, d in zip(names, r.stdout.splitlines())}
+    plain = _plain(names)
     res, cur = [], []
     for ln in out.splitlines():
         w = ln.split()

@@ -30,3 +30,19 @@ def test_time_march_stays_launchable(rule, call, shape):
         assert "bwdt_kernel" in [x.name for x in ls]
         for x in ls:
             assert x.blocks * x.threads < 1 << 32, x
+
+
+CALLS = ("fwd", "fwdR", "fwd_ws", "bwd", "vg", "vg_ws", "bc", "vjp", "vjp_acc")
+# grids of a few nodes to a few times 10^7, narrow and wide rows
+GRIDS = {2: [(9, 50), (128, 256), (700, 900), (3000, 3000)],
+         3: [(9, 10, 40), (64, 64, 64), (150, 131, 257), (256, 256, 256)],
+         4: [(5, 9, 10, 40), (10, 32, 32, 32), (22, 29, 32, 28), (14, 56, 55, 83),
+             (20, 128, 128, 128)]}
+
+
+def test_every_kernel_is_reached(rule):
+    """The library holds no kernel that the rule never launches."""
+    req = [(call, op, shape, bc) for op, spec in W.OPS.items() for shape in GRIDS[spec.ndim]
+           for bc in (0, 1) for call in CALLS]
+    seen = {x.kernel for ls in L.launches(rule, req) for x in ls}
+    assert L.kernels(rule) == seen
