@@ -432,8 +432,11 @@ Chunks plan_chunks(const Dims& n, int TX, int TY, int res, Sum sum, double prolo
         const double k = queue ? (double)rest / kCUs : (double)((rest + kCUs - 1) / kCUs);
         const double last = queue ? 1.0 / res + (1.0 - 1.0 / res) * k / res : 0.3 + 0.7 * k / res;
         double cost = (zc + prologue) * ((double)full + (rest ? last : 0.0));
-        if (sum == Sum::atomics) cost += 0.015 * (double)(W < round ? W : round);
-        if (sum == Sum::workspace && W > kGroup) cost += 0.8;
+        // (a launch with more workgroups than the workspace has slots adds atomically)
+        if (sum == Sum::atomics || (sum == Sum::workspace && W > kWsMaxBlocks))
+            cost += 0.015 * (double)(W < round ? W : round);
+        else if (sum == Sum::workspace && W > kGroup)
+            cost += 0.8;
         if (best.cost == 0.0 || cost < best.cost) best = {zc, cost};
     }
     return best;
@@ -622,14 +625,19 @@ int launch_fwd2(const Req& r, bool store, double* loss) {
 template <class GEO, class OP>
 int launch_bwd2(const Req& r, const double* dloss, double* loss) {
     if constexpr (FPDE_BWD2_QUEUE) {
-        auto run = [&](auto t) {
-            using T = decltype(t);
-            const int zc =
-                plan_chunks(r.dims, T::TX, 1, T::RES, loss_sum(r, loss), GEO::PROLOGUE, true).zc;
-            return launch_bwdq<OP, T::TX / 62>(r, dloss, zc, loss);
+        auto run = [&](auto t, int zc) {
+            return launch_bwdq<OP, decltype(t)::TX / 62>(r, dloss, zc, loss);
         };
-        if (loss_sum(r, loss) == Sum::atomics) return run(typename GEO::TBA{});
-        return run(typename GEO::TB{});
+        auto plan = [&](auto t, Sum sum) {
+            using T = decltype(t);
+            return plan_chunks(r.dims, T::TX, 1, T::RES, sum, GEO::PROLOGUE, true).zc;
+        };
+        using T = typename GEO::TB;
+        const int zc = plan(T{}, loss_sum(r, loss));
+        // the loss by atomics: no workspace, or a launch with more workgroups than it holds
+        if (loss && !(r.ws && tile_dims(r.dims, T::TX, 1, zc).nblocks <= kWsMaxBlocks))
+            return run(typename GEO::TBA{}, plan(typename GEO::TBA{}, Sum::atomics));
+        return run(T{}, zc);
     } else {
         const int zc = plan_chunks(r.dims, FPDE_TX2, 1, 4, loss_sum(r, loss), kPrologue).zc;
         return launch_bwd<OP, FPDE_TX2, 1>(r, dloss, zc, loss);

@@ -46,3 +46,17 @@ def test_every_kernel_is_reached(rule):
            for bc in (0, 1) for call in CALLS]
     seen = {x.kernel for ls in L.launches(rule, req) for x in ls}
     assert L.kernels(rule) == seen
+
+
+@pytest.mark.parametrize("op,shape", [(W.POISSON_2D, (5, 4_500_000)),
+                                      (W.HELMHOLTZ_2D, (40, 5_000_000)),
+                                      (W.NS_2D_STEADY, (6, 4_300_000)),
+                                      (W.HEAT_3D_BE, (9, 1100, 8000)),
+                                      (W.NS_3D_BE, (9, 600, 8100))],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_more_workgroups_than_the_workspace_holds(rule, op, shape):
+    """Such a launch sums its loss by atomics and is planned so: what the call with a
+    workspace queues is what the call without one queues."""
+    for call in ("fwd", "vg"):
+        plain, ws = L.launches(rule, [(call, op, shape, 0), (call + "_ws", op, shape, 0)])
+        assert ws[-1].blocks > 4096 and plain == ws, (plain, ws)
