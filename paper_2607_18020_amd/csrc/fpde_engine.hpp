@@ -863,7 +863,11 @@ __global__ __launch_bounds__(TX* TY, (kBwdMinW<OP, TX * TY>)) void bwd_kernel(Pt
     // column holds the residual that column's gather needs as its x+1 term)
     const uint32_t cbr =
         PER ? (uint32_t)(wrap_idx(gy, D.ny) * D.nx + wrap_idx(gx, D.nx)) * 4u : cb;
-    const float scale = (float)(two_over_M * (*dloss));
+    float scale = (float)(two_over_M * (*dloss));
+    // (in a VGPR: in an SGPR, the one too many of the interior value and gradient of four
+    // fields, it had the compiler reserve a private segment; the others keep theirs, NS-3D
+    // steady 256^3 backward 131.8 us, 134.6 with it)
+    if (LOSS && !PER) asm volatile("" : "+v"(scale));
 
     PS ps;
     ps.init(t, [&](int i, int& lin) {

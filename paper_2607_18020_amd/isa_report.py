@@ -181,6 +181,8 @@ def violations(kernels: Dict[str, dict]) -> List[str]:
             bad.append(f"{name}: {c['pk_f32']} packed-FP32 instructions")
         if c["scratch_ops"]:
             bad.append(f"{name}: {c['scratch_ops']} scratch accesses (register spills)")
+        if c["scratch"]:
+            bad.append(f"{name}: a private segment of {c['scratch']} bytes")
         if reduces_loss(name):
             if c["atomic"] != 1:
                 bad.append(f"{name}: {c['atomic']} atomic instructions, expected one")
@@ -204,7 +206,7 @@ def report(kernels: Dict[str, dict], command: str, match=("",)) -> str:
            "`atomic`: global atomics (one float64 add, executed by one thread per "
            "workgroup, in the kernels that reduce the loss); `scratch`: the private segment "
            "the compiler reserves (bytes), `scratch_ops`: instructions that use it (spills); "
-           "`mfma`, `pk_f32`, `scratch_ops`: must be 0.",
+           "`mfma`, `pk_f32`, `scratch`, `scratch_ops`: must be 0.",
            "", "| kernel | " + " | ".join(cols) + " |", "|---|" + "---|" * len(cols)]
     for name in sorted(kernels):
         if any(m in name for m in match):

@@ -2,8 +2,8 @@
 plane loads streamed straight into LDS and LDS stencil reads in the marching
 kernels, a DPP wavefront sum and exactly one float64 atomic instruction in the
 kernels that reduce the loss, no atomics in the gather-form backward, the
-boundary kernel or the vjp, no MFMA, no packed-FP32 VALU and no register
-spills anywhere."""
+boundary kernel or the vjp, no MFMA, no packed-FP32 VALU, no register spills
+and no private segment anywhere."""
 from __future__ import annotations
 
 import os
