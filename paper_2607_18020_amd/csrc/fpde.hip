@@ -106,76 +106,97 @@ namespace {
 #endif
 constexpr bool kBwdReverse = FPDE_BWD_REVERSE != 0;
 
-// planes' worth of time that a chunk's march spends before its first step
-constexpr double kPrologue = 2.5;
-// A TX x TY tile of columns; RES workgroups of it run on a CU at once (by the
-// kernel's LDS and threads), which plan_chunks sizes a launch for, and a step of
-// a full round takes STEP percent of the wide tile's.
-template <int TX_, int TY_, int RES_, int STEP_ = 100>
+// A TX x TY tile of columns.  RES workgroups of its kernel run on a CU at once, by the
+// kernel's LDS, threads and registers (a test compares it with the compiler's own resource
+// notes), RESL of the kernel that also sums the loss and RESP of that one on a periodic
+// grid, where they need more registers; a step of a full round of them takes STEP
+// percent of the wide tile's.
+template <int TX_, int TY_, int RES_, int STEP_ = 100, int RESL_ = RES_, int RESP_ = RESL_>
 struct Tile {
     static constexpr int TX = TX_, TY = TY_, RES = RES_, STEP = STEP_;
+    static constexpr int res(bool loss, bool per) { return !loss ? RES : per ? RESP_ : RESL_; }
 };
-// 3-D grids: forward, backward and explicit-sensitivity backward tiles, each a
-// wide one (fewer cache lines shared across tile edges: the faster on wide rows)
-// and a narrow one, which leaves fewer lanes idle where the last axis is not a
-// multiple of the wide tile, and whose smaller workgroups have the shorter step
-// on a grid that does not fill the chip; with_tile picks.
-template <class F, class F2, class B, class B2, class V, class V2, bool QF = false, int RF = 4>
-struct Geo3 {
-    static constexpr bool D3 = true;
-    static constexpr bool FWD_QUEUE = QF;  // forward: fwdq_kernel (else the LDS march)
-    static constexpr int FWD_RING = RF;    // LDS march forward: slots of its plane ring
-    // the 8-slot ring's prologue loads seven planes
-    static constexpr double FWD_PROLOGUE = RF == 8 ? 5.0 : kPrologue;
-    using TF = F;
-    using TF2 = F2;
-    using TB = B;
-    using TB2 = B2;
-    using TV = V;
-    using TV2 = V2;
+// One kind of launch: its wide tile W (fewer cache lines shared across tile edges: the
+// faster on wide rows) and its narrow one N, which leaves fewer lanes idle where the last
+// axis is not a multiple of the wide tile, and whose smaller workgroups have the shorter
+// step on a grid that does not fill the chip (with_tile picks); and how the march's time
+// goes (share, floor, prologue, atom: plan_chunks).  STEP is the ratio of the two tiles'
+// full rounds; the others are fitted per kind.  Both from the times of either tile at some 25
+// chunk counts each, on 150 to 330 grids per operator of 2^16 to 2^25 nodes: the launches
+// that the rule takes are within 0 to 3% of the fastest one measured in the geometric mean
+// and 30% at worst, stored residuals of heat and 3D+t apart (4 and 9%).  One share and
+// prologue for every march, and the residency of one kernel for all that share a tile, had
+// the forwards 3 to 10% off.
+template <class W_, class N_ = W_>
+struct Plan {
+    using W = W_;
+    using N = N_;
+    double share, floor, prologue, atom = 0.012;
 };
-// 2-D grids: row segments (TY = 1).  The register-queue kernels start with Q - 1
-// rows in flight, about as long as five steps; RF, RF2, RB: workgroups of the wide
-// and the narrow forward and of the backward per CU (by their VGPRs).  The wide
-// forward wins where the narrow one's loss atomics would be more (NS-2D 2048^2
-// without a workspace: 15.2 us in 256 workgroups of 1024, 17.7 in 512 of 256); the
-// narrow one on short rows and small grids (374 x 447: 7.9 and 7.0 us; Burgers
-// 128 x 256: 5.9 and 4.7, 5.5 of each the launches), and with a workspace
-// (Helmholtz 1024^2: 8.0 and 7.4).
-// RBA waves per workgroup where the value and gradient sums its loss by atomics: one
-// field's workgroups finish together, and half as many of eight waves wait for half
-// the atomics (Helmholtz 2048^2 19.4 -> 17.7 us, 901 x 480 9.1 -> 8.4, Burgers
-// 1397 x 1661 13.8 -> 11.7); three fields are no faster so (2048^2 26.7 -> 28.0).
-template <int RF, int RF2, int RB, int RBA>
-struct Geo2 {
+// 2-D grids: row segments (TY = 1).  The wide forward wins where the narrow one's loss
+// atomics would be more (NS-2D 2048^2 without a workspace: 15.2 us in 256 workgroups of
+// 1024, 17.7 in 512 of 256); the narrow one on short rows and small grids (374 x 447:
+// 7.9 and 7.0 us; Burgers 128 x 256: 5.9 and 4.7, 5.5 of each the launches), and with a
+// workspace (Helmholtz 1024^2: 8.0 and 7.4).
+// VGA: where the value and gradient sums its loss by atomics.  One field's workgroups
+// finish together, and half as many of eight waves wait for half the atomics (Helmholtz
+// 2048^2 19.4 -> 17.7 us, 901 x 480 9.1 -> 8.4, Burgers 1397 x 1661 13.8 -> 11.7); three
+// fields are no faster so (2048^2 26.7 -> 28.0).
+template <int RL, int RLA>  // value and gradient: workgroups of four and of eight waves per CU
+struct Geo2One {
     static constexpr bool D3 = false;
-    static constexpr double PROLOGUE = 5.0;
-    using TF = Tile<FPDE_TX2_FWD, 1, RF>;
-    using TF2 = Tile<256, 1, RF2, 98>;
-    using TB = Tile<62 * FPDE_BWD2_NW, 1, RB>;
-    using TBA = Tile<62 * RBA, 1, RB * FPDE_BWD2_NW / RBA>;
-    using TV = Tile<FPDE_TX2, 1, 4>;
-    using TV2 = TV;
+    static constexpr Plan<Tile<FPDE_TX2_FWD, 1, 2>, Tile<256, 1, 8, 140>> FWD{0.85, 0, 3.5},
+        FWDR{0.85, 0, 3.5};
+    [[maybe_unused]] static constexpr Plan<Tile<62 * FPDE_BWD2_NW, 1, 8>> BWD{1.0, 0, 5.0};
+    [[maybe_unused]] static constexpr Plan<Tile<62 * FPDE_BWD2_NW, 1, 8, 100, RL>> VG{0.9, 0, 4.5};
+    [[maybe_unused]] static constexpr Plan<Tile<62 * 8, 1, 4, 100, RLA>> VGA{0.9, 0, 4.5};
+    static constexpr Plan<Tile<FPDE_TX2, 1, 8>> VJP{0.2, 0, 5.0};
 };
-using Geo2One = Geo2<2, 8, 8, 8>;  // one field: up to 64 VGPRs (the value and gradient 78)
-using Geo2NS = Geo2<1, 4, 3, FPDE_BWD2_NW>;   // three: 120, backward 152
-// several fields with nonlinear coupling (NS): two 512-thread forward workgroups
-// per CU (57 KB of LDS each), one 1024-thread backward (148 KB) or two 512-thread
-// ones (79 KB), two 256-thread explicit-sensitivity ones (57 KB).  The narrow
-// tiles' steps, measured on grids of many full rounds: forward 87 -> 91 us at
-// 256^3 and 28.1 -> 28.6 at 245 x 233 x 127; backward 154 -> 173 and 58.6 ->
-// 60.4.  Where they win: NS-3D backward 150 x 131 x 257 61 -> 54 us (5 tiles of 64
-// across a row instead of 3 of 128), 64^3 10.8 -> 8.1, 28 x 39 x 47 9.0 -> 7.0;
-// forward 64^3 10.4 -> 8.6 (5.5 of it the loss fill and the launches).
-using GeoNS3 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>, Tile<64, 8, 2, 104>,
-                    Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>, Tile<64, 8, 2, 106>,
-                    Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>, Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
+using Geo2Burgers = Geo2One<8, 4>;   // 45 VGPRs with the loss
+using Geo2Laplace = Geo2One<6, 3>;   // Helmholtz, Poisson: 76 to 78
+struct Geo2NS {
+    static constexpr bool D3 = false;
+    static constexpr Plan<Tile<FPDE_TX2_FWD, 1, 1>, Tile<256, 1, 4>> FWD{0.9, 0, 4.0};
+    static constexpr Plan<Tile<FPDE_TX2_FWD, 1, 1>, Tile<256, 1, 4, 94>> FWDR{0, 1.6, 1.5};
+    [[maybe_unused]] static constexpr Plan<Tile<62 * FPDE_BWD2_NW, 1, 3>> BWD{0, 1.2, 1.5};
+    [[maybe_unused]] static constexpr Plan<Tile<62 * FPDE_BWD2_NW, 1, 3, 100, 3, 2>>
+        VG{0, 1.6, 5.0}, VGA{0, 1.6, 5.0};  // (152 to 174 VGPRs)
+    static constexpr Plan<Tile<FPDE_TX2, 1, 5>> VJP{0, 2.2, 2.5};
+};
+// 3-D grids.  Several fields with nonlinear coupling (NS): the LDS decides, but for the
+// wide backward's 1024 threads.  Where the narrow tiles win: NS-3D backward
+// 150 x 131 x 257 61 -> 54 us (5 tiles of 64 across a row instead of 3 of 128), 64^3
+// 10.8 -> 8.1, 28 x 39 x 47 9.0 -> 7.0; forward 64^3 10.4 -> 8.6 (5.5 of it the loss fill
+// and the launches).
+struct GeoNS3 {
+    static constexpr bool D3 = true, FWD_QUEUE = false;  // (forward: the LDS march)
+    static constexpr int FWD_RING = 4;                   // slots of the forward's plane ring
+    using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>;
+    using TB = Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>;
+    static constexpr Plan<TF, Tile<64, 8, 3, 152>> FWD{0, 1.45, 2.5};
+    static constexpr Plan<TF, Tile<64, 8, 3, 155>> FWDR{0, 1.6, 2.5};
+    static constexpr Plan<TB, Tile<64, 8, 2, 104>> BWD{0, 1.3, 2.5};
+    static constexpr Plan<TB, Tile<64, 8, 2, 103>> VG{0, 1.3, 2.5, 0.005};
+    static constexpr Plan<Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>> VJP{0, 1.6, 2.5};
+};
+// 2D+t: one field less, so more workgroups per CU
+struct GeoNST {
+    static constexpr bool D3 = true, FWD_QUEUE = false;
+    static constexpr int FWD_RING = 4;
+    using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 3>;
+    using TB = Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>;
+    static constexpr Plan<TF, Tile<64, 8, 4, 140>> FWD{0, 1.6, 2.5};
+    static constexpr Plan<TF, Tile<64, 8, 4, 142>> FWDR{0, 1.6, 5.0};
+    static constexpr Plan<TB, Tile<64, 8, 2, 101>> BWD{0, 1.3, 2.5};
+    static constexpr Plan<TB, Tile<64, 8, 2, 101>> VG{0, 1.3, 2.5, 0.005};
+    static constexpr Plan<Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 4>> VJP{0, 1.6, 2.5};
+};
 // 3D+t NS: the forward and the explicit-sensitivity backward run the 3-D marches
 // on one time level per workgroup; the backward marches time (bwdt_kernel) over
-// blocks of TZ x TY x TX nodes with NT threads.  STEP: one level's time, percent of
-// the first one's (4.75, 6.3, 3.75 us on an idle chip, 6.2, 8.7, 4.65 on a full one);
-// launch_bwdt takes the block with the shortest estimated march: the larger ones
-// evaluate fewer residuals per node (1.65, 1.56, 1.81), the smaller ones fill more
+// blocks of TZ x TY x TX nodes with NT threads, one workgroup per CU.  STEP: one level's
+// time, percent of the first one's (4.75, 6.3, 3.75 us on an idle chip, 6.2, 8.7, 4.65 on a
+// full one); launch_bwdt takes the block with the shortest estimated march: the larger
+// ones evaluate fewer residuals per node (1.65, 1.56, 1.81), the smaller ones fill more
 // CUs.  Backward at 20 x 128^3 710, 656, 705 us; 14 x 56 x 55 x 83 70, 81, 79;
 // 22 x 29 x 32 x 28 29, 31, 24 (815, 102, 66 with a level march and a time pass).
 template <int TZ_, int TY_, int TX_, int NT_, int STEP_>
@@ -188,18 +209,30 @@ using Blocks4 = std::tuple<Block4<4, 4, 64, 1024, 100>>;
 using Blocks4 =
     std::tuple<Block4<8, 6, 32, 768, 100>, Block4<8, 8, 32, 512, 140>, Block4<4, 8, 32, 1024, 75>>;
 #endif
-using GeoNS4 = Geo3<Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>, Tile<64, 8, 2, 104>, void, void,
-                    Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>, Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>>;
+struct GeoNS4 {
+    static constexpr bool D3 = true, FWD_QUEUE = false;
+    static constexpr int FWD_RING = 4;
+    using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>;
+    static constexpr Plan<TF, Tile<64, 8, 3, 150>> FWD{0.3, 0, 3.0};
+    static constexpr Plan<TF, Tile<64, 8, 3, 140>> FWDR{0.4, 0, 1.5};
+    static constexpr Plan<void> BWDT{0.3, 0, 2.2, 0.0025};  // (its tiles: Blocks4)
+    static constexpr Plan<Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>> VJP{0.3, 0, 2.5};
+};
 // one field, a Laplacian (heat, Poisson): 1024-thread wide forward and
 // explicit-sensitivity workgroups, the others 512 threads, bound by the 2048
-// threads of a CU.  The narrow forward: 28.6 -> 29.6 us at 256^3, 11.8 -> 8.4 at
-// 97 x 90 x 41 and 9.1 -> 6.9 at 44 x 56 x 32; explicit sensitivities 26.1 -> 26.8,
+// threads of a CU.  The narrow forward, full rounds: 28.6 -> 29.6 us at 256^3; but 11.8 ->
+// 8.4 at 97 x 90 x 41 and 9.1 -> 6.9 at 44 x 56 x 32; explicit sensitivities 26.1 -> 26.8,
 // 6.0 -> 4.8 and 4.6 -> 3.8.  (The backward's wide tile is a 64-node one.)
-using GeoHeat = Geo3<Tile<FPDE_HEAT_FWD_TX, FPDE_HEAT_FWD_TY, 2>, Tile<64, 8, 4, 103>,
-                     Tile<FPDE_HEAT_BWD_TX, FPDE_HEAT_BWD_TY, 4>,
-                     Tile<FPDE_HEAT_BWD_TX, FPDE_HEAT_BWD_TY, 4>,
-                     Tile<FPDE_VJP_HEAT_TX, FPDE_VJP_HEAT_TY, 2>, Tile<64, 8, 4, 103>,
-                     FPDE_HEAT_FWD_QUEUE != 0, FPDE_HEAT_FWD_RING>;
+struct GeoHeat {
+    static constexpr bool D3 = true, FWD_QUEUE = FPDE_HEAT_FWD_QUEUE != 0;
+    [[maybe_unused]] static constexpr int FWD_RING = FPDE_HEAT_FWD_RING;
+    static constexpr Plan<Tile<FPDE_HEAT_FWD_TX, FPDE_HEAT_FWD_TY, 2>, Tile<64, 8, 4, 104>>
+        FWD{0.3, 0, 5.0, 0.016}, FWDR{0.3, 0, 5.0, 0.016};
+    static constexpr Plan<Tile<FPDE_HEAT_BWD_TX, FPDE_HEAT_BWD_TY, 4>> BWD{0.14, 0, 3.0},
+        VG{0.43, 0, 3.4};
+    static constexpr Plan<Tile<FPDE_VJP_HEAT_TX, FPDE_VJP_HEAT_TY, 2>, Tile<64, 8, 4, 102>>
+        VJP{0.2, 0, 5.0};
+};
 
 template <class OP_, class GEO_>
 struct OpTag {
@@ -212,15 +245,15 @@ struct OpTag {
 template <class F>
 int with_op(int op, F&& f) {
     switch (op) {
-    case FPDE_BURGERS_1DT: return f(OpTag<OpBurgers, Geo2One>{});
-    case FPDE_HELMHOLTZ_2D: return f(OpTag<OpHelmholtz, Geo2One>{});
+    case FPDE_BURGERS_1DT: return f(OpTag<OpBurgers, Geo2Burgers>{});
+    case FPDE_HELMHOLTZ_2D: return f(OpTag<OpHelmholtz, Geo2Laplace>{});
     case FPDE_HEAT_3D_BE: return f(OpTag<OpHeat, GeoHeat>{});
     case FPDE_NS_2D_STEADY: return f(OpTag<OpNS2, Geo2NS>{});
     case FPDE_NS_3D_BE: return f(OpTag<OpNS3, GeoNS3>{});
     case FPDE_NS_3D_STEADY: return f(OpTag<OpNS3S, GeoNS3>{});
-    case FPDE_POISSON_2D: return f(OpTag<OpPoisson<2>, Geo2One>{});
+    case FPDE_POISSON_2D: return f(OpTag<OpPoisson<2>, Geo2Laplace>{});
     case FPDE_POISSON_3D: return f(OpTag<OpPoisson<3>, GeoHeat>{});
-    case FPDE_NS_2DT: return f(OpTag<OpNST, GeoNS3>{});
+    case FPDE_NS_2DT: return f(OpTag<OpNST, GeoNST>{});
     // 3D+t: the 3-D marches run on one time level per workgroup
     case FPDE_NS_3DT: return f(OpTag<OpNS3T, GeoNS4>{});
     }
@@ -381,24 +414,26 @@ Dims tile_dims(const Dims& n, int TX, int TY, int zc) {
     return dm;
 }
 
-// Chunk length of a march with TX x TY tiles of which RES workgroups fit a
-// CU at once.  A launch runs in rounds of CUs * RES workgroups, each as long as
-// one chunk's march (its planes plus about kPrologue planes' worth of prologue:
-// the first planes' latency and the halo planes' residuals), so a launch a little over a whole
+// Chunk length of a march with TX x TY tiles of which `res` workgroups fit a
+// CU at once.  A launch runs in rounds of CUs * res workgroups, each as long as
+// one chunk's march (its planes plus `prologue` planes' worth of the first planes' latency
+// and the halo planes' residuals), so a launch a little over a whole
 // number of rounds idles most of the chip in its last one: at 150 x 131 x 257 the
 // NS-3D backward takes 93 us cut into 306 workgroups and 61 us cut into 255, and
 // the 2D+t one at 33 x 201 x 259 28 us in 312 and 20 us in 234.  The rule takes,
 // among the chunk counts that just fill 1, 2, ... CUs' worth of workgroups, the
-// one with the shortest estimated march.  In a last round with k of RES
-// workgroups per CU a step of an LDS march costs 0.3 + 0.7 k / RES of a full
-// round's, the fullest CU deciding (NS-3D, two per CU: 0.65 at one; heat 97 x 90 x 41
-// backward 6.3 us in 228 workgroups, 7.2 in 288); one of a register-queue march,
-// whose waves wait for nobody, 1 / RES + (1 - 1 / RES) k / RES, its
-// latency and then its throughput (2-D backward, eight per CU, us per row at 1, 2, 3.8,
-// 6.5 and 8: 0.22, 0.26, 0.40, 0.66, 0.8).
-// A loss costs one atomic per workgroup of the last round, serialised at 12 ns,
-// about 0.015 of a step, or through a workspace a second level of slots beyond 64
-// workgroups, about 1 us or 0.8 of a step.
+// one with the shortest estimated march.  In a last round with k of res
+// workgroups per CU (LDS marches: on the fullest CU) a step takes, of a full round's,
+//     max(floor / res, s + (1 - s) k / res),
+// s (the march's share, a register-queue march's share / res) the latency that remains
+// however few there are, and floor the workgroups that it takes to fill a CU's bandwidth:
+// one field's marches go by the first (measured, k = 1 .. res: heat backward 0.38, 0.56,
+// 0.77, 1; 2-D backward 0.28 at one, 0.33 at two of eight), several fields' by the second
+// (NS-3D narrow forward 0.45, 0.68, 1; 2D+t explicit sensitivities 0.45, 0.55, 0.75, 1;
+// NS-2D ones 0.37, 0.47, 0.60, 0.78, 1).
+// A loss costs one atomic per workgroup of the last round, serialised at 12 ns, `atom`
+// of a step (0.012, and 0.0025 of a level of the time march), or through a workspace a
+// second level of slots beyond 64 workgroups, as much as 65 of them.
 enum class Sum { none, atomics, workspace };
 #ifndef FPDE_CUS
 #define FPDE_CUS 256
@@ -406,13 +441,19 @@ enum class Sum { none, atomics, workspace };
 constexpr int kCUs = FPDE_CUS;
 struct Chunks {
     int zc;       // planes per chunk
-    double cost;  // estimated time, in steps of a full round
+    double cost;  // estimated time, in steps of a full round of the wide tile's workgroups
 };
-Chunks plan_chunks(const Dims& n, int TX, int TY, int res, Sum sum, double prologue,
+template <class P>
+Chunks plan_chunks(const Dims& n, int TX, int TY, int res, int step, Sum sum, const P& p,
                    bool queue = false) {
     const long long tiles =
         (long long)((n.nx + TX - 1) / TX) * ((n.ny + TY - 1) / TY) * n.nlev;
     const int nplanes = n.nz - 2 * n.zlo;
+    const double s = queue ? p.share / res : p.share;
+    auto part = [&](double k) {  // a step with k workgroups per CU, of a full round's
+        const double v = s + (1.0 - s) * k / res, least = p.floor / res;
+        return v > least ? v : least < 1.0 ? least : 1.0;
+    };
     Chunks best = {nplanes, 0.0};
     long long tried = 0;
     // an eighth, a quarter, half of the CUs; CU loads 1 .. res (one round, in
@@ -430,16 +471,21 @@ Chunks plan_chunks(const Dims& n, int TX, int TY, int res, Sum sum, double prolo
         const long long round = (long long)kCUs * res, full = W / round;
         const long long rest = W - full * round;
         const double k = queue ? (double)rest / kCUs : (double)((rest + kCUs - 1) / kCUs);
-        const double last = queue ? 1.0 / res + (1.0 - 1.0 / res) * k / res : 0.3 + 0.7 * k / res;
-        double cost = (zc + prologue) * ((double)full + (rest ? last : 0.0));
+        double cost = (zc + p.prologue) * ((double)full + (rest ? part(k) : 0.0)) * step / 100.0;
         // (a launch with more workgroups than the workspace has slots adds atomically)
         if (sum == Sum::atomics || (sum == Sum::workspace && W > kWsMaxBlocks))
-            cost += 0.015 * (double)(W < round ? W : round);
+            cost += p.atom * (double)(W < round ? W : round);
         else if (sum == Sum::workspace && W > kGroup)
-            cost += 0.8;
+            cost += 65.0 * p.atom;
         if (best.cost == 0.0 || cost < best.cost) best = {zc, cost};
     }
     return best;
+}
+// ... of a launch of tile T of plan p
+template <class T, class P>
+Chunks plan_tile(const P& p, const Dims& n, Sum sum, bool queue) {
+    return plan_chunks(n, T::TX, T::TY, T::res(sum != Sum::none, n.per != 0), T::STEP, sum, p,
+                       queue);
 }
 
 int check_outputs(const Req& r, const fpde_grid4*, const float* const* fields,
@@ -577,14 +623,16 @@ Sum loss_sum(const Req& r, const double* loss) {
     return !loss ? Sum::none : r.ws ? Sum::workspace : Sum::atomics;
 }
 
-// f(Tile<...>{}, zc) for the wide tile A or (if narrow) the narrow tile B of a
-// 3-D launch, whichever has the shorter estimated march (plan_chunks)
-template <class A, class B, bool QUEUE = false, class F>
-int with_tile(const Dims& n, Sum sum, double prologue, bool narrow, F&& f) {
-    const Chunks a = plan_chunks(n, A::TX, A::TY, A::RES, sum, prologue, QUEUE);
+// f(Tile<...>{}, zc) for the wide or (if narrow) the narrow tile of a plan, whichever has
+// the shorter estimated march (plan_chunks)
+template <bool QUEUE = false, class P, class F>
+int with_tile(const P& p, const Dims& n, Sum sum, bool narrow, F&& f) {
+    using A = typename P::W;
+    using B = typename P::N;
+    const Chunks a = plan_tile<A>(p, n, sum, QUEUE);
     if (!std::is_same<A, B>::value && narrow) {
-        const Chunks b = plan_chunks(n, B::TX, B::TY, B::RES, sum, prologue, QUEUE);
-        if (b.cost * B::STEP < a.cost * A::STEP) return f(B{}, b.zc);
+        const Chunks b = plan_tile<B>(p, n, sum, QUEUE);
+        if (b.cost < a.cost) return f(B{}, b.zc);
     }
     return f(A{}, a.zc);
 }
@@ -596,31 +644,36 @@ int with_tile(const Dims& n, Sum sum, double prologue, bool narrow, F&& f) {
 template <class GEO, class OP>
 int launch_fwd3(const Req& r, bool store, double* loss) {
     const bool narrow = !store || r.N * OP::NR * 4 <= (32LL << 20);
-    return with_tile<typename GEO::TF, typename GEO::TF2, GEO::FWD_QUEUE>(
-        r.dims, loss_sum(r, loss), GEO::FWD_PROLOGUE, narrow, [&](auto t, int zc) {
-            using T = decltype(t);
-            if constexpr (GEO::FWD_QUEUE)
-                return launch_fwdq<OP, T::TX, T::TY>(r, store, loss, zc);
-            else
-                return launch_fwd<OP, T::TX, T::TY, GEO::FWD_RING>(r, store, loss, zc);
-        });
+    auto go = [&](auto t, int zc) {
+        using T = decltype(t);
+        if constexpr (GEO::FWD_QUEUE)
+            return launch_fwdq<OP, T::TX, T::TY>(r, store, loss, zc);
+        else
+            return launch_fwd<OP, T::TX, T::TY, GEO::FWD_RING>(r, store, loss, zc);
+    };
+    const Sum sum = loss_sum(r, loss);
+    return store ? with_tile<GEO::FWD_QUEUE>(GEO::FWDR, r.dims, sum, narrow, go)
+                 : with_tile<GEO::FWD_QUEUE>(GEO::FWD, r.dims, sum, narrow, go);
 }
 template <class GEO, class OP>
 int launch_bwd3(const Req& r, const double* dloss, double* loss) {
-    return with_tile<typename GEO::TB, typename GEO::TB2>(
-        r.dims, loss_sum(r, loss), kPrologue, true, [&](auto t, int zc) {
-            using T = decltype(t);
-            return launch_bwd<OP, T::TX, T::TY>(r, dloss, zc, loss);
-        });
+    auto go = [&](auto t, int zc) {
+        using T = decltype(t);
+        return launch_bwd<OP, T::TX, T::TY>(r, dloss, zc, loss);
+    };
+    return loss ? with_tile(GEO::VG, r.dims, loss_sum(r, loss), true, go)
+                : with_tile(GEO::BWD, r.dims, Sum::none, true, go);
 }
 
 // 2-D launches
 template <class GEO, class OP>
 int launch_fwd2(const Req& r, bool store, double* loss) {
-    return with_tile<typename GEO::TF, typename GEO::TF2, true>(
-        r.dims, loss_sum(r, loss), GEO::PROLOGUE, true, [&](auto t, int zc) {
-            return launch_fwdq<OP, decltype(t)::TX, 1>(r, store, loss, zc);
-        });
+    auto go = [&](auto t, int zc) {
+        return launch_fwdq<OP, decltype(t)::TX, 1>(r, store, loss, zc);
+    };
+    const Sum sum = loss_sum(r, loss);
+    return store ? with_tile<true>(GEO::FWDR, r.dims, sum, true, go)
+                 : with_tile<true>(GEO::FWD, r.dims, sum, true, go);
 }
 template <class GEO, class OP>
 int launch_bwd2(const Req& r, const double* dloss, double* loss) {
@@ -628,18 +681,17 @@ int launch_bwd2(const Req& r, const double* dloss, double* loss) {
         auto run = [&](auto t, int zc) {
             return launch_bwdq<OP, decltype(t)::TX / 62>(r, dloss, zc, loss);
         };
-        auto plan = [&](auto t, Sum sum) {
-            using T = decltype(t);
-            return plan_chunks(r.dims, T::TX, 1, T::RES, sum, GEO::PROLOGUE, true).zc;
-        };
-        using T = typename GEO::TB;
-        const int zc = plan(T{}, loss_sum(r, loss));
-        // the loss by atomics: no workspace, or a launch with more workgroups than it holds
-        if (loss && !(r.ws && tile_dims(r.dims, T::TX, 1, zc).nblocks <= kWsMaxBlocks))
-            return run(typename GEO::TBA{}, plan(typename GEO::TBA{}, Sum::atomics));
-        return run(T{}, zc);
+        if (!loss) return with_tile<true>(GEO::BWD, r.dims, Sum::none, false, run);
+        if (r.ws) {
+            using T = typename decltype(GEO::VG)::W;
+            const int zc = plan_tile<T>(GEO::VG, r.dims, Sum::workspace, true).zc;
+            if (tile_dims(r.dims, T::TX, 1, zc).nblocks <= kWsMaxBlocks) return run(T{}, zc);
+        }
+        // no workspace, or a launch with more workgroups than it holds
+        return with_tile<true>(GEO::VGA, r.dims, Sum::atomics, false, run);
     } else {
-        const int zc = plan_chunks(r.dims, FPDE_TX2, 1, 4, loss_sum(r, loss), kPrologue).zc;
+        const int zc =
+            plan_chunks(r.dims, FPDE_TX2, 1, 4, 100, loss_sum(r, loss), GEO::VJP).zc;
         return launch_bwd<OP, FPDE_TX2, 1>(r, dloss, zc, loss);
     }
 }
@@ -694,14 +746,14 @@ int launch_bwdt(const Req& r, const double* dloss, double* loss, std::tuple<T...
         using B = decltype(t);
         q.nx = ((r.dims.nx + B::TX - 1) / B::TX) * ((r.dims.ny + B::TY - 1) / B::TY) *
                ((r.dims.nz + B::TZ - 1) / B::TZ);
-        const Chunks c = plan_chunks(q, 1, 1, 1, loss_sum(r, loss), 2.0);
+        const Chunks c = plan_chunks(q, 1, 1, 1, B::STEP, loss_sum(r, loss), GeoNS4::BWDT);
         // (a launch holds fewer than 2^32 threads: on a level a few nodes thin, where a
         // block is mostly empty, the blocks with more threads per node are out; the
         // 8 x 8 x 32 ones, half a thread each, fit every level)
-        if ((long long)q.nx * B::NT < (1LL << 32) && (best < 0 || c.cost * B::STEP < cost)) {
+        if ((long long)q.nx * B::NT < (1LL << 32) && (best < 0 || c.cost < cost)) {
             best = i;
             zc = c.zc;
-            cost = c.cost * B::STEP;
+            cost = c.cost;
         }
         ++i;
     };
@@ -733,8 +785,8 @@ int run_vjp(const Req& r, bool acc) {
     return with_op(r.op, [&](auto tag) {
         using OP = typename decltype(tag)::OP;
         using GEO = typename decltype(tag)::GEO;
-        return with_tile<typename GEO::TV, typename GEO::TV2>(
-            base, Sum::none, kPrologue, true, [&](auto t, int zc) {
+        return with_tile(
+            GEO::VJP, base, Sum::none, true, [&](auto t, int zc) {
                 using T = decltype(t);
                 return launch_vjp<OP, T::TX, T::TY>(r, acc, base, zc);
             });

@@ -8,8 +8,10 @@
  * with call one of fwd, fwdR (residuals stored), fwd_ws, bwd, vg, vg_ws, bc, vjp, vjp_acc.
  * One answer per launch,
  *     <device kernel name> <workgroups> <threads> [<chunk length> <tiles_x> <tiles_y>]
- * (the bracket for the marching kernels), then "= <status>".  With an argument: the
- * names of the library's kernels instead.
+ * (the bracket for the marching kernels), then "= <status>".  With the argument
+ * "kernels": the names of the library's kernels instead; with "residency": what the rule
+ * takes for the workgroups of each tile per CU, one line per tile,
+ *     <fwd|fwdR|bwd|vg|vjp> <op> <tile width> <height> <not periodic> <periodic>
  */
 #include "fpde.hip"
 
@@ -45,9 +47,36 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
 }
 }
 
-int main(int argc, char**) {
+template <class T>
+static void show_tile(const char* kind, int op, bool loss) {
+    printf("%s %d %d %d %d %d\n", kind, op, T::TX, T::TY, T::res(loss, false), T::res(loss, true));
+}
+template <class P>
+static void show(const char* kind, int op, const P&, bool loss) {
+    show_tile<typename P::W>(kind, op, loss);
+    show_tile<typename P::N>(kind, op, loss);
+}
+static void show_residency() {
+    for (int op = FPDE_BURGERS_1DT; op <= FPDE_NS_3DT; ++op)
+        fpde::with_op(op, [&](auto tag) {
+            using GEO = typename decltype(tag)::GEO;
+            show("fwd", op, GEO::FWD, true);
+            show("fwdR", op, GEO::FWDR, true);
+            show("vjp", op, GEO::VJP, false);
+            if constexpr (!decltype(tag)::OP::TIME) {  // (the time march: one per CU)
+                show("bwd", op, GEO::BWD, false);
+                show("vg", op, GEO::VG, true);
+                if constexpr (!GEO::D3) show("vg", op, GEO::VGA, true);
+            }
+            return FPDE_OK;
+        });
+}
+
+int main(int argc, char** argv) {
     if (argc > 1) {
-        for (const auto& k : g_names) printf("%s\n", k.second.c_str());
+        if (!strcmp(argv[1], "residency")) show_residency();
+        else
+            for (const auto& k : g_names) printf("%s\n", k.second.c_str());
         return 0;
     }
     // device addresses far apart, never dereferenced

@@ -63,6 +63,13 @@ def kernels(exe: str) -> set:
     return set(_plain(names.split()).values())
 
 
+def residency(exe: str):
+    """(kind, op, tile width, tile height, workgroups per CU, the same on a periodic grid)
+    for every tile of the rule."""
+    out = subprocess.run([exe, "residency"], capture_output=True, text=True, check=True).stdout
+    return sorted({(w[0], *map(int, w[1:])) for w in map(str.split, out.splitlines())})
+
+
 def launches(exe: str, requests) -> List[List[Launch]]:
     """For each (call, op, shape, bc_mode): its launches.  Every call must succeed."""
     text = "".join(f"{call} {op} {bc} {len(shape)} {' '.join(map(str, shape))}\n"

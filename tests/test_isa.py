@@ -12,6 +12,8 @@ import shutil
 import pytest
 
 from paper_2607_18020_amd import isa_report as R
+from paper_2607_18020_amd import workloads as W
+from tests import launch_rule as L
 
 pytestmark = pytest.mark.skipif(shutil.which(R.B.HIPCC) is None and not os.path.exists(R.B.HIPCC),
                                 reason="hipcc not available")
@@ -128,3 +130,50 @@ def test_eight_slot_forward_waits(asm, store_r, per):
         else:
             seg.append(t)
     assert steps >= RD  # the unrolled march and its tail
+
+
+def test_launch_rule_residency(kernels, tmp_path):
+    """The launch rule sizes a launch by how many workgroups of the kernel a CU holds:
+    for every tile, what the compiler's resource notes give (LDS, threads, registers)."""
+    exe = L.compile_rule(tmp_path)
+    shape = {2: (40, 300), 3: (9, 40, 300), 4: (5, 9, 40, 300)}
+    ops = {op: L.launches(exe, [("vjp", op, shape[spec.ndim], 0)])[0][0].kernel.split("<", 1)[1]
+           for op, spec in W.OPS.items()}
+    ops = {op: k[:k.rindex(", 64, ") if ", 64, " in k else k.index(", 128, ") if ", 128, " in k
+                 else k.index(", 256, ")] for op, k in ops.items()}
+    checked = set()
+    for kind, op, tx, ty, *want in L.residency(exe):
+        name = ops[op]
+        for name_k, c in kernels.items():
+            fn, args = name_k.split("<")[0], R._template_args(name_k) if "<" in name_k else []
+            if not args or args[0] != name:
+                continue
+            a = args[1:]
+            if kind in ("fwd", "fwdR") and fn in ("fwd_kernel", "fwdq_kernel"):
+                tile = a[:2]
+                flags = a[2:4] if fn == "fwd_kernel" else a[3:5]
+                if flags[0] != str(kind == "fwdR").lower():
+                    continue
+                per, nt = flags[1], int(a[0]) * int(a[1])
+            elif kind in ("bwd", "vg") and fn == "bwd_kernel":
+                tile, per, nt = a[:2], a[4], int(a[0]) * int(a[1])
+                if a[3] != str(kind == "vg").lower():
+                    continue
+            elif kind in ("bwd", "vg") and fn == "bwdq_kernel":
+                tile, per, nt = [str(62 * int(a[0])), "1"], a[3], 64 * int(a[0])
+                if a[2] != str(kind == "vg").lower():
+                    continue
+            elif kind == "vjp" and fn == "vjp_kernel":
+                tile, per, nt = a[:2], a[3], int(a[0]) * int(a[1])
+            else:
+                continue
+            if tile == [str(tx), str(ty)]:
+                assert c["occupancy"] * 4 // (nt // 64) == want[per == "true"], (kind, name_k)
+                checked.add(name_k)
+    # every marching kernel; the time march is planned with one workgroup per CU
+    for name_k, c in kernels.items():
+        if name_k.startswith("bwdt_kernel"):
+            assert c["occupancy"] * 4 // (int(R._template_args(name_k)[4]) // 64) == 1, name_k
+        elif name_k.split("<")[0] in ("fwd_kernel", "fwdq_kernel", "bwd_kernel", "bwdq_kernel",
+                                      "vjp_kernel"):
+            assert name_k in checked, name_k

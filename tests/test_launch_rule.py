@@ -35,7 +35,8 @@ def test_time_march_stays_launchable(rule, call, shape):
 CALLS = ("fwd", "fwdR", "fwd_ws", "bwd", "vg", "vg_ws", "bc", "vjp", "vjp_acc")
 # grids of a few nodes to a few times 10^7, narrow and wide rows
 GRIDS = {2: [(9, 50), (128, 256), (700, 900), (3000, 3000)],
-         3: [(9, 10, 40), (64, 64, 64), (150, 131, 257), (256, 256, 256)],
+         3: [(9, 10, 40), (64, 64, 64), (150, 131, 257), (256, 256, 256), (40, 4, 128),
+             (66, 64, 512), (300, 300, 300)],
          4: [(5, 9, 10, 40), (10, 32, 32, 32), (22, 29, 32, 28), (14, 56, 55, 83),
              (20, 128, 128, 128)]}
 
