@@ -124,7 +124,7 @@ struct Tile {
 // full rounds; the others are fitted per kind.  Both from the times of either tile at some 25
 // chunk counts each, on 150 to 330 grids per operator of 2^16 to 2^25 nodes: the launches
 // that the rule takes are within 0 to 3% of the fastest one measured in the geometric mean
-// and 30% at worst, stored residuals of heat and 3D+t apart (4 and 9%).  One share and
+// and 32% at worst.  One share and
 // prologue for every march, and the residency of one kernel for all that share a tile, had
 // the forwards 3 to 10% off.
 template <class W_, class N_ = W_>
@@ -171,6 +171,7 @@ struct Geo2NS {
 struct GeoNS3 {
     static constexpr bool D3 = true, FWD_QUEUE = false;  // (forward: the LDS march)
     static constexpr int FWD_RING = 4;                   // slots of the forward's plane ring
+    static constexpr double STORE_EDGE = 1.4;            // (launch_fwd3)
     using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>;
     using TB = Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>;
     static constexpr Plan<TF, Tile<64, 8, 3, 152>> FWD{0, 1.45, 2.5};
@@ -183,6 +184,7 @@ struct GeoNS3 {
 struct GeoNST {
     static constexpr bool D3 = true, FWD_QUEUE = false;
     static constexpr int FWD_RING = 4;
+    static constexpr double STORE_EDGE = 1.4;
     using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 3>;
     using TB = Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>;
     static constexpr Plan<TF, Tile<64, 8, 4, 140>> FWD{0, 1.6, 2.5};
@@ -212,6 +214,7 @@ using Blocks4 =
 struct GeoNS4 {
     static constexpr bool D3 = true, FWD_QUEUE = false;
     static constexpr int FWD_RING = 4;
+    static constexpr double STORE_EDGE = 1.4;
     using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>;
     static constexpr Plan<TF, Tile<64, 8, 3, 150>> FWD{0.3, 0, 3.0};
     static constexpr Plan<TF, Tile<64, 8, 3, 140>> FWDR{0.4, 0, 1.5};
@@ -226,6 +229,7 @@ struct GeoNS4 {
 struct GeoHeat {
     static constexpr bool D3 = true, FWD_QUEUE = FPDE_HEAT_FWD_QUEUE != 0;
     [[maybe_unused]] static constexpr int FWD_RING = FPDE_HEAT_FWD_RING;
+    static constexpr double STORE_EDGE = 1.0;
     static constexpr Plan<Tile<FPDE_HEAT_FWD_TX, FPDE_HEAT_FWD_TY, 2>, Tile<64, 8, 4, 104>>
         FWD{0.3, 0, 5.0, 0.016}, FWDR{0.3, 0, 5.0, 0.016};
     static constexpr Plan<Tile<FPDE_HEAT_BWD_TX, FPDE_HEAT_BWD_TY, 4>> BWD{0.14, 0, 3.0},
@@ -623,27 +627,30 @@ Sum loss_sum(const Req& r, const double* loss) {
     return !loss ? Sum::none : r.ws ? Sum::workspace : Sum::atomics;
 }
 
-// f(Tile<...>{}, zc) for the wide or (if narrow) the narrow tile of a plan, whichever has
-// the shorter estimated march (plan_chunks)
+// f(Tile<...>{}, zc) for the wide or the narrow tile of a plan, whichever has the shorter
+// estimated march (plan_chunks), the narrow one's times `extra`
 template <bool QUEUE = false, class P, class F>
-int with_tile(const P& p, const Dims& n, Sum sum, bool narrow, F&& f) {
+int with_tile(const P& p, const Dims& n, Sum sum, double extra, F&& f) {
     using A = typename P::W;
     using B = typename P::N;
     const Chunks a = plan_tile<A>(p, n, sum, QUEUE);
-    if (!std::is_same<A, B>::value && narrow) {
+    if (!std::is_same<A, B>::value) {
         const Chunks b = plan_tile<B>(p, n, sum, QUEUE);
-        if (b.cost < a.cost) return f(B{}, b.zc);
+        if (extra * b.cost < a.cost) return f(B{}, b.zc);
     }
     return f(A{}, a.zc);
 }
 
-// Residual stores beyond the 32 MB of the L2s keep the wide tile: rows of a
-// ragged grid are not aligned to cache lines, and each tile edge splits one
-// between two workgroups' non-temporal stores (NS-3D 150 x 131 x 257, forward
-// with residuals: 47 us with 128-wide tiles, 58 with 64-wide ones).
+// Residual stores beyond the 32 MB of the L2s: rows of a ragged grid are not aligned to
+// cache lines, and each tile edge splits one between two workgroups' non-temporal stores
+// (NS-3D 150 x 131 x 257: 47 us with 128-wide tiles, 58 with 64-wide ones), so the narrow
+// tile's march costs STORE_EDGE times as much: 1.4 for several fields, nothing for one.  (It
+// was ruled out there, which left half the lanes of a wide tile idle on rows of up to 64
+// nodes and a few more: 3D+t forwards with residuals up to 1.9, heat ones up to 1.6 times the
+// narrow tile's time.)
 template <class GEO, class OP>
 int launch_fwd3(const Req& r, bool store, double* loss) {
-    const bool narrow = !store || r.N * OP::NR * 4 <= (32LL << 20);
+    const double extra = store && r.N * OP::NR * 4 > (32LL << 20) ? GEO::STORE_EDGE : 1.0;
     auto go = [&](auto t, int zc) {
         using T = decltype(t);
         if constexpr (GEO::FWD_QUEUE)
@@ -652,8 +659,8 @@ int launch_fwd3(const Req& r, bool store, double* loss) {
             return launch_fwd<OP, T::TX, T::TY, GEO::FWD_RING>(r, store, loss, zc);
     };
     const Sum sum = loss_sum(r, loss);
-    return store ? with_tile<GEO::FWD_QUEUE>(GEO::FWDR, r.dims, sum, narrow, go)
-                 : with_tile<GEO::FWD_QUEUE>(GEO::FWD, r.dims, sum, narrow, go);
+    return store ? with_tile<GEO::FWD_QUEUE>(GEO::FWDR, r.dims, sum, extra, go)
+                 : with_tile<GEO::FWD_QUEUE>(GEO::FWD, r.dims, sum, extra, go);
 }
 template <class GEO, class OP>
 int launch_bwd3(const Req& r, const double* dloss, double* loss) {
@@ -661,8 +668,8 @@ int launch_bwd3(const Req& r, const double* dloss, double* loss) {
         using T = decltype(t);
         return launch_bwd<OP, T::TX, T::TY>(r, dloss, zc, loss);
     };
-    return loss ? with_tile(GEO::VG, r.dims, loss_sum(r, loss), true, go)
-                : with_tile(GEO::BWD, r.dims, Sum::none, true, go);
+    return loss ? with_tile(GEO::VG, r.dims, loss_sum(r, loss), 1.0, go)
+                : with_tile(GEO::BWD, r.dims, Sum::none, 1.0, go);
 }
 
 // 2-D launches
@@ -672,8 +679,8 @@ int launch_fwd2(const Req& r, bool store, double* loss) {
         return launch_fwdq<OP, decltype(t)::TX, 1>(r, store, loss, zc);
     };
     const Sum sum = loss_sum(r, loss);
-    return store ? with_tile<true>(GEO::FWDR, r.dims, sum, true, go)
-                 : with_tile<true>(GEO::FWD, r.dims, sum, true, go);
+    return store ? with_tile<true>(GEO::FWDR, r.dims, sum, 1.0, go)
+                 : with_tile<true>(GEO::FWD, r.dims, sum, 1.0, go);
 }
 template <class GEO, class OP>
 int launch_bwd2(const Req& r, const double* dloss, double* loss) {
@@ -681,14 +688,14 @@ int launch_bwd2(const Req& r, const double* dloss, double* loss) {
         auto run = [&](auto t, int zc) {
             return launch_bwdq<OP, decltype(t)::TX / 62>(r, dloss, zc, loss);
         };
-        if (!loss) return with_tile<true>(GEO::BWD, r.dims, Sum::none, false, run);
+        if (!loss) return with_tile<true>(GEO::BWD, r.dims, Sum::none, 1.0, run);
         if (r.ws) {
             using T = typename decltype(GEO::VG)::W;
             const int zc = plan_tile<T>(GEO::VG, r.dims, Sum::workspace, true).zc;
             if (tile_dims(r.dims, T::TX, 1, zc).nblocks <= kWsMaxBlocks) return run(T{}, zc);
         }
         // no workspace, or a launch with more workgroups than it holds
-        return with_tile<true>(GEO::VGA, r.dims, Sum::atomics, false, run);
+        return with_tile<true>(GEO::VGA, r.dims, Sum::atomics, 1.0, run);
     } else {
         const int zc =
             plan_chunks(r.dims, FPDE_TX2, 1, 4, 100, loss_sum(r, loss), GEO::VJP).zc;
@@ -786,7 +793,7 @@ int run_vjp(const Req& r, bool acc) {
         using OP = typename decltype(tag)::OP;
         using GEO = typename decltype(tag)::GEO;
         return with_tile(
-            GEO::VJP, base, Sum::none, true, [&](auto t, int zc) {
+            GEO::VJP, base, Sum::none, 1.0, [&](auto t, int zc) {
                 using T = decltype(t);
                 return launch_vjp<OP, T::TX, T::TY>(r, acc, base, zc);
             });

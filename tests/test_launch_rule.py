@@ -4,6 +4,7 @@ from __future__ import annotations
 
 import os
 
+import numpy as np
 import pytest
 
 from paper_2607_18020_amd import workloads as W
@@ -61,3 +62,17 @@ def test_more_workgroups_than_the_workspace_holds(rule, op, shape):
     for call in ("fwd", "vg"):
         plain, ws = L.launches(rule, [(call, op, shape, 0), (call + "_ws", op, shape, 0)])
         assert ws[-1].blocks > 4096 and plain == ws, (plain, ws)
+
+
+@pytest.mark.parametrize("op,shape", [(W.NS_3DT, (14, 40, 60, 64)), (W.NS_3DT, (20, 60, 60, 40)),
+                                      (W.HEAT_3D_BE, (440, 300, 64)),
+                                      (W.NS_3D_BE, (200, 200, 60))],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_stored_residuals_on_short_rows(rule, op, shape):
+    """More residuals than the L2s hold, on rows that a 64-node tile covers: the forward
+    takes it, and leaves no half of a wide tile idle."""
+    assert 4 * len(W.OPS[op].residuals) * float(np.prod(shape)) > 2 ** 25
+    for bc in (0, 1):
+        (ls,) = L.launches(rule, [("fwdR", op, shape, bc)])
+        march = [x for x in ls if x.name == "fwd_kernel"]
+        assert [x.args[:2] for x in march] == [("64", "8")], march
