@@ -187,7 +187,7 @@ struct GeoNST {
     static constexpr double STORE_EDGE = 1.4;
     using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 3>;
     using TB = Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>;
-    static constexpr Plan<TF, Tile<64, 8, 4, 140>> FWD{0, 1.6, 2.5};
+    static constexpr Plan<TF, Tile<64, 8, 4, 140>> FWD{0.1, 1.6, 2.5};
     static constexpr Plan<TF, Tile<64, 8, 4, 142>> FWDR{0, 1.6, 5.0};
     static constexpr Plan<TB, Tile<64, 8, 2, 101>> BWD{0, 1.3, 2.5};
     static constexpr Plan<TB, Tile<64, 8, 2, 101>> VG{0, 1.3, 2.5, 0.005};

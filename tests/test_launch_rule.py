@@ -76,3 +76,16 @@ def test_stored_residuals_on_short_rows(rule, op, shape):
         (ls,) = L.launches(rule, [("fwdR", op, shape, bc)])
         march = [x for x in ls if x.name == "fwd_kernel"]
         assert [x.args[:2] for x in march] == [("64", "8")], march
+
+
+@pytest.mark.parametrize("shape", [(305, 495, 196), (237, 186, 637), (343, 278, 307)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_large_2dt_forward_fills_its_round(rule, shape):
+    """On grids whose fields do not fit the caches, two of the three workgroups that a CU
+    holds are 1.2 times slower than three: the forward takes a full round, or nearly."""
+    (ls,) = L.launches(rule, [("fwd", W.NS_2DT, shape, 0)])
+    x = ls[-1]
+    per_round = 256 * (3 if x.args[0] == "128" else 4)
+    rounds = x.blocks / per_round
+    assert x.name == "fwd_kernel" and rounds > 0.6 and abs(rounds - round(rounds)) < 0.33, x
+    assert x.blocks > 512, x
