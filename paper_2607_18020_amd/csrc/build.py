@@ -43,10 +43,10 @@ FLAGS = [
 CHECK_LIB = os.path.join(PKG, "libfpde_check.so")
 CHECK_FLAGS = [
     "-DFPDE_LDS_POISON=1",
-    "-DFPDE_NS3_FWD_TX=64", "-DFPDE_NS3_FWD_TY=8", "-DFPDE_NS3_BWD_TX=64", "-DFPDE_NS3_BWD_TY=16",
-    "-DFPDE_CUS=90", "-DFPDE_HEAT_FWD_TX=128", "-DFPDE_HEAT_BWD_TX=128",
-    "-DFPDE_VJP_TY3=8", "-DFPDE_VJP_HEAT_TX=64",
-    "-DFPDE_TX2=128", "-DFPDE_TX2_FWD=512",
+    "-DFPDE_NS3_FWD_TY=8", "-DFPDE_NS3_FWD2_TY=4", "-DFPDE_NS3_BWD_TX=64", "-DFPDE_NS3_BWD_TY=16",
+    "-DFPDE_NS3_BWD2_TY=4", "-DFPDE_CUS=90", "-DFPDE_HEAT_FWD_TX=128", "-DFPDE_HEAT_FWD2_TY=4",
+    "-DFPDE_HEAT_BWD_TX=128", "-DFPDE_VJP_TY3=8", "-DFPDE_VJP_HEAT_TX=64", "-DFPDE_VJP_HEAT_TY=16",
+    "-DFPDE_VJP_HEAT2_TY=4", "-DFPDE_TX2=128", "-DFPDE_TX2_FWD=512", "-DFPDE_TX2_FWD2=128",
     "-DFPDE_FWD2_Q=4", "-DFPDE_HEAT_FWD_QUEUE=1", "-DFPDE_T4_CHECK",
     "-DFPDE_BWD2_QUEUE=0",
 ]

@@ -48,6 +48,16 @@ namespace {
 #ifndef FPDE_HEAT_BWD_TY
 #define FPDE_HEAT_BWD_TY 8
 #endif
+// rows of the narrow 64-node tiles
+#ifndef FPDE_NS3_FWD2_TY
+#define FPDE_NS3_FWD2_TY 8
+#endif
+#ifndef FPDE_NS3_BWD2_TY
+#define FPDE_NS3_BWD2_TY 8
+#endif
+#ifndef FPDE_HEAT_FWD2_TY
+#define FPDE_HEAT_FWD2_TY 8
+#endif
 // 2-D rows of the LDS marches (explicit-sensitivity backward; the checking
 // build's backward) and of the register-queue forward (the wide ones)
 #ifndef FPDE_TX2
@@ -55,6 +65,9 @@ namespace {
 #endif
 #ifndef FPDE_TX2_FWD
 #define FPDE_TX2_FWD 1024
+#endif
+#ifndef FPDE_TX2_FWD2
+#define FPDE_TX2_FWD2 256
 #endif
 // register-queue forward: planes held per lane (the centre plane, its two
 // neighbours, and Q - 3 planes in flight)
@@ -99,6 +112,9 @@ namespace {
 #endif
 #ifndef FPDE_VJP_HEAT_TY
 #define FPDE_VJP_HEAT_TY 8
+#endif
+#ifndef FPDE_VJP_HEAT2_TY
+#define FPDE_VJP_HEAT2_TY 8
 #endif
 // The backward marches each chunk top-down (see above).
 #ifndef FPDE_BWD_REVERSE
@@ -145,7 +161,7 @@ struct Plan {
 template <int RL, int RLA>  // value and gradient: workgroups of four and of eight waves per CU
 struct Geo2One {
     static constexpr bool D3 = false;
-    static constexpr Plan<Tile<FPDE_TX2_FWD, 1, 2>, Tile<256, 1, 8, 140>> FWD{0.85, 0, 3.5},
+    static constexpr Plan<Tile<FPDE_TX2_FWD, 1, 2>, Tile<FPDE_TX2_FWD2, 1, 8, 140>> FWD{0.85, 0, 3.5},
         FWDR{0.85, 0, 3.5};
     [[maybe_unused]] static constexpr Plan<Tile<62 * FPDE_BWD2_NW, 1, 8>> BWD{1.0, 0, 5.0};
     [[maybe_unused]] static constexpr Plan<Tile<62 * FPDE_BWD2_NW, 1, 8, 100, RL>> VG{0.9, 0, 4.5};
@@ -156,8 +172,8 @@ using Geo2Burgers = Geo2One<8, 4>;   // 45 VGPRs with the loss
 using Geo2Laplace = Geo2One<6, 3>;   // Helmholtz, Poisson: 76 to 78
 struct Geo2NS {
     static constexpr bool D3 = false;
-    static constexpr Plan<Tile<FPDE_TX2_FWD, 1, 1>, Tile<256, 1, 4>> FWD{0.9, 0, 4.0};
-    static constexpr Plan<Tile<FPDE_TX2_FWD, 1, 1>, Tile<256, 1, 4, 94>> FWDR{0, 1.6, 1.5};
+    static constexpr Plan<Tile<FPDE_TX2_FWD, 1, 1>, Tile<FPDE_TX2_FWD2, 1, 4>> FWD{0.9, 0, 4.0};
+    static constexpr Plan<Tile<FPDE_TX2_FWD, 1, 1>, Tile<FPDE_TX2_FWD2, 1, 4, 94>> FWDR{0, 1.6, 1.5};
     [[maybe_unused]] static constexpr Plan<Tile<62 * FPDE_BWD2_NW, 1, 3>> BWD{0, 1.2, 1.5};
     [[maybe_unused]] static constexpr Plan<Tile<62 * FPDE_BWD2_NW, 1, 3, 100, 3, 2>>
         VG{0, 1.6, 5.0}, VGA{0, 1.6, 5.0};  // (152 to 174 VGPRs)
@@ -174,10 +190,10 @@ struct GeoNS3 {
     static constexpr double STORE_EDGE = 1.4;            // (launch_fwd3)
     using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>;
     using TB = Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>;
-    static constexpr Plan<TF, Tile<64, 8, 3, 152>> FWD{0, 1.45, 2.5};
-    static constexpr Plan<TF, Tile<64, 8, 3, 155>> FWDR{0, 1.6, 2.5};
-    static constexpr Plan<TB, Tile<64, 8, 2, 104>> BWD{0, 1.3, 2.5};
-    static constexpr Plan<TB, Tile<64, 8, 2, 103>> VG{0, 1.3, 2.5, 0.005};
+    static constexpr Plan<TF, Tile<64, FPDE_NS3_FWD2_TY, 3, 152>> FWD{0, 1.45, 2.5};
+    static constexpr Plan<TF, Tile<64, FPDE_NS3_FWD2_TY, 3, 155>> FWDR{0, 1.6, 2.5};
+    static constexpr Plan<TB, Tile<64, FPDE_NS3_BWD2_TY, 2, 104>> BWD{0, 1.3, 2.5};
+    static constexpr Plan<TB, Tile<64, FPDE_NS3_BWD2_TY, 2, 103>> VG{0, 1.3, 2.5, 0.005};
     static constexpr Plan<Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>> VJP{0, 1.6, 2.5};
 };
 // 2D+t: one field less, so more workgroups per CU
@@ -187,10 +203,10 @@ struct GeoNST {
     static constexpr double STORE_EDGE = 1.4;
     using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 3>;
     using TB = Tile<FPDE_NS3_BWD_TX, FPDE_NS3_BWD_TY, 1>;
-    static constexpr Plan<TF, Tile<64, 8, 4, 140>> FWD{0.1, 1.6, 2.5};
-    static constexpr Plan<TF, Tile<64, 8, 4, 142>> FWDR{0, 1.6, 5.0};
-    static constexpr Plan<TB, Tile<64, 8, 2, 101>> BWD{0, 1.3, 2.5};
-    static constexpr Plan<TB, Tile<64, 8, 2, 101>> VG{0, 1.3, 2.5, 0.005};
+    static constexpr Plan<TF, Tile<64, FPDE_NS3_FWD2_TY, 4, 140>> FWD{0.1, 1.6, 2.5};
+    static constexpr Plan<TF, Tile<64, FPDE_NS3_FWD2_TY, 4, 142>> FWDR{0, 1.6, 5.0};
+    static constexpr Plan<TB, Tile<64, FPDE_NS3_BWD2_TY, 2, 101>> BWD{0, 1.3, 2.5};
+    static constexpr Plan<TB, Tile<64, FPDE_NS3_BWD2_TY, 2, 101>> VG{0, 1.3, 2.5, 0.005};
     static constexpr Plan<Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 4>> VJP{0, 1.6, 2.5};
 };
 // 3D+t NS: the forward and the explicit-sensitivity backward run the 3-D marches
@@ -216,8 +232,8 @@ struct GeoNS4 {
     static constexpr int FWD_RING = 4;
     static constexpr double STORE_EDGE = 1.4;
     using TF = Tile<FPDE_NS3_FWD_TX, FPDE_NS3_FWD_TY, 2>;
-    static constexpr Plan<TF, Tile<64, 8, 3, 150>> FWD{0.3, 0, 3.0};
-    static constexpr Plan<TF, Tile<64, 8, 3, 140>> FWDR{0.4, 0, 1.5};
+    static constexpr Plan<TF, Tile<64, FPDE_NS3_FWD2_TY, 3, 150>> FWD{0.3, 0, 3.0};
+    static constexpr Plan<TF, Tile<64, FPDE_NS3_FWD2_TY, 3, 140>> FWDR{0.4, 0, 1.5};
     static constexpr Plan<void> BWDT{0.3, 0, 2.2, 0.0025};  // (its tiles: Blocks4)
     static constexpr Plan<Tile<FPDE_VJP_TX3, FPDE_VJP_TY3, 2>> VJP{0.3, 0, 2.5};
 };
@@ -230,11 +246,13 @@ struct GeoHeat {
     static constexpr bool D3 = true, FWD_QUEUE = FPDE_HEAT_FWD_QUEUE != 0;
     [[maybe_unused]] static constexpr int FWD_RING = FPDE_HEAT_FWD_RING;
     static constexpr double STORE_EDGE = 1.0;
-    static constexpr Plan<Tile<FPDE_HEAT_FWD_TX, FPDE_HEAT_FWD_TY, 2>, Tile<64, 8, 4, 104>>
+    static constexpr Plan<Tile<FPDE_HEAT_FWD_TX, FPDE_HEAT_FWD_TY, 2>,
+                          Tile<64, FPDE_HEAT_FWD2_TY, 4, 104>>
         FWD{0.3, 0, 5.0, 0.016}, FWDR{0.3, 0, 5.0, 0.016};
     static constexpr Plan<Tile<FPDE_HEAT_BWD_TX, FPDE_HEAT_BWD_TY, 4>> BWD{0.14, 0, 3.0},
         VG{0.43, 0, 3.4};
-    static constexpr Plan<Tile<FPDE_VJP_HEAT_TX, FPDE_VJP_HEAT_TY, 2>, Tile<64, 8, 4, 102>>
+    static constexpr Plan<Tile<FPDE_VJP_HEAT_TX, FPDE_VJP_HEAT_TY, 2>,
+                          Tile<64, FPDE_VJP_HEAT2_TY, 4, 102>>
         VJP{0.2, 0, 5.0};
 };
 

@@ -89,3 +89,22 @@ def test_large_2dt_forward_fills_its_round(rule, shape):
     rounds = x.blocks / per_round
     assert x.name == "fwd_kernel" and rounds > 0.6 and abs(rounds - round(rounds)) < 0.33, x
     assert x.blocks > 512, x
+
+
+@pytest.fixture(scope="module")
+def check_rule(tmp_path_factory):
+    return L.compile_rule(tmp_path_factory.mktemp("check_rule"), B.CHECK_FLAGS)
+
+
+def test_checking_build_runs_other_tiles(rule, check_rule):
+    """The GPU test that compares the two builds bit for bit needs a different tile (or
+    algorithm) in each: every marching launch of every one of its cases."""
+    from tests.test_gpu_check_build import CASES  # noqa: PLC0415
+    req = [(call, W.CONFIGS[cfg].op, shape, bc) for cfg, shape in CASES for bc in (0, 1)
+           for call in ("fwdR", "bwd", "vg", "vjp")]
+    for what, a, b in zip(req, L.launches(rule, req), L.launches(check_rule, req)):
+        a, b = ([x for x in ls if x.tiles] for ls in (a, b))
+        a, b = ([x for x in ls if not x.name.startswith(("bc", "zero"))] for ls in (a, b))
+        assert len(a) == len(b) == 1
+        tile = lambda x: (x.name, *x.args[:4 if x.name == "bwdt_kernel" else 2])  # noqa: E731
+        assert tile(a[0]) != tile(b[0]), (what, a, b)
