@@ -4,6 +4,7 @@ slots changes shape, against the call without a workspace."""
 from __future__ import annotations
 
 import ctypes
+import os
 
 import pytest
 
@@ -39,19 +40,50 @@ def test_workspace_arguments(ws, status):
 
 def test_workspace_size():
     from paper_2607_18020_amd import binding as B  # noqa: PLC0415
-    import os  # noqa: PLC0415
     import re  # noqa: PLC0415
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     src = open(os.path.join(root, "include", "fpde.h")).read()
     assert int(re.search(r"#define FPDE_WORKSPACE_BYTES (\d+)", src).group(1)) == B.WORKSPACE_BYTES
 
 
-# one workgroup; a full group of 64 and one more; two levels with a last group of
-# one; the most workgroups the slots hold, and one more (no workspace then)
-SHAPES = [(W.BURGERS_1DT, (3, 50)), (W.BURGERS_1DT, (66, 70)), (W.BURGERS_1DT, (67, 70)),
-          (W.HELMHOLTZ_2D, (195, 1500)), (W.BURGERS_1DT, (3, 1024 * 4096)),
-          (W.BURGERS_1DT, (3, 1024 * 4096 + 1)), (W.NS_3D_STEADY, (30, 40, 70)),
-          (W.HEAT_3D_BE, (64, 65, 66)), (W.NS_3DT, (5, 12, 20, 40))]
+# (operator, grid): what the calls with a workspace launch, (workgroups of the forward, of
+# the value and gradient).  One workgroup; a full group of 64 and one more, as one row of
+# workgroups or several; a last group of one behind two full ones and a ragged one; the 64
+# full groups of the slots, and one workgroup more, which adds by atomics (the value and
+# gradient of one field takes half as many wider ones then, which the slots hold again)
+COUNTS = {
+    (W.BURGERS_1DT, (3, 50)): (1, 3),
+    (W.BURGERS_1DT, (66, 70)): (64, 33),
+    (W.BURGERS_1DT, (67, 70)): (33, 34),
+    (W.BURGERS_1DT, (3, 16385)): (65, 67),
+    (W.BURGERS_1DT, (3, 15873)): (63, 65),
+    (W.HELMHOLTZ_2D, (3, 32769)): (129, 133),
+    (W.HELMHOLTZ_2D, (195, 1500)): (234, 231),
+    (W.NS_2D_STEADY, (3, 1015808)): (3968, 4096),
+    (W.BURGERS_1DT, (3, 1015809)): (993, 2049),
+    (W.BURGERS_1DT, (3, 1024 * 4096)): (4096, 8457),
+    (W.BURGERS_1DT, (3, 1024 * 4096 + 1)): (4097, 8457),
+    (W.NS_3D_STEADY, (30, 40, 70)): (140, 150),
+    (W.HEAT_3D_BE, (64, 65, 66)): (234, 396),
+    (W.NS_3DT, (5, 12, 20, 40)): (150, 54),
+}
+SHAPES = list(COUNTS)
+
+
+def test_workgroup_counts(tmp_path):
+    """The grids below launch the workgroup counts that they stand for, and up to 4096 of
+    them without the fill that the sum by atomics needs (so they go through the slots)."""
+    from paper_2607_18020_amd.csrc import build as build_mod  # noqa: PLC0415
+    from tests import launch_rule as L  # noqa: PLC0415
+    if not os.path.exists(build_mod.HIPCC):
+        pytest.skip("hipcc not available")
+    exe = L.compile_rule(tmp_path)
+    for (op, shape), want in COUNTS.items():
+        for call, n in zip(("fwd_ws", "vg_ws"), want):
+            (ls,) = L.launches(exe, [(call, op, shape, 0)])
+            march = [x for x in ls if x.tiles and not x.name.startswith("bc")]
+            assert [x.blocks for x in march] == [n], (shape, call, ls)
+            assert ("fill_f64_kernel" in [x.name for x in ls]) == (n > 4096), (shape, call, ls)
 
 
 @pytest.mark.gpu
