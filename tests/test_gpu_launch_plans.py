@@ -1,7 +1,7 @@
-"""3-D launches at the sizes where the launch rule changes its mind: a chunk
-count that just fills or just misses a round of workgroups, one-plane chunks, a
-last chunk of one plane, a single chunk, more tiles than a round holds, and the
-wide and narrow tiles of each kernel (ragged against both).
+"""3-D launches at the sizes where the launch rule changes its mind: one-plane chunks,
+a last chunk of one plane, a single chunk, more tiles than a round of workgroups holds,
+and the wide and narrow tiles of each kernel, ragged against both.
+(tests/test_launch_rule.py holds the launches to that.)
 Every entry point against the oracle, node by node, in both boundary modes."""
 from __future__ import annotations
 
@@ -14,21 +14,27 @@ from tests import gpu_helpers as H
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    (W.NS_3D_BE, (3, 40, 130)),      # one interior plane
-    (W.NS_3D_BE, (67, 64, 66)),      # one- and two-plane chunks, two tiles per row
-    (W.NS_3D_STEADY, (62, 9, 129)),  # one plane per chunk, a last tile of one column
-    (W.NS_2DT, (5, 290, 520)),       # more tiles than a round of the backward holds
+    (W.NS_3D_BE, (3, 40, 130)),      # one interior plane; one-plane chunks with the loss
+    (W.NS_3D_BE, (67, 64, 66)),      # five-plane chunks, two tiles per row
+    (W.NS_3D_STEADY, (62, 9, 129)),  # two- and three-plane chunks, a last tile of one column
+    (W.NS_2DT, (5, 290, 520)),       # single chunks
     (W.NS_3D_BE, (17, 33, 193)),     # narrow backward tiles, a last one of one column
-    (W.HEAT_3D_BE, (37, 33, 65)),    # narrow forward and explicit-sensitivity tiles
-    (W.HEAT_3D_BE, (20, 41, 255)),   # wide ones
+    (W.NS_2DT, (17, 33, 193)),
+    (W.HEAT_3D_BE, (37, 33, 65)),    # narrow tiles; a last chunk of one plane
+    (W.HEAT_3D_BE, (20, 41, 255)),   # wide forward tiles
     (W.POISSON_3D, (70, 12, 257)),
+    (W.NS_3D_BE, (5, 290, 1200)),    # more tiles than a round holds, of every kernel
+    (W.NS_2DT, (4, 400, 1000)),      # the same, wide backward tiles
+    (W.HEAT_3D_BE, (3, 500, 1030)),  # and one field's
+    (W.HEAT_3D_BE, (5, 300, 520)),   # wide explicit-sensitivity tiles
     (W.NS_3DT, (4, 19, 13, 131)),
-    # the time-marching backward's blocks: 4x8x32 (one chunk of levels per level, and
-    # two chunks), 8x6x32 and 8x8x32, ragged against each
+    # the time-marching backward's blocks: 4x8x32 (one chunk of levels per level, two
+    # chunks, one), 8x8x32 and 8x6x32, ragged against each
     (W.NS_3DT, (5, 9, 21, 33)),
     (W.NS_3DT, (12, 21, 47, 90)),
     (W.NS_3DT, (5, 17, 41, 65)),
     (W.NS_3DT, (5, 64, 57, 123)),
+    (W.NS_3DT, (9, 33, 34, 34)),
 ]
 
 

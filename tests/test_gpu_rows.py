@@ -1,8 +1,9 @@
 """2-D launches at the edges of their row segments and chunks: rows of one wave's
-62 output columns and one more, the 248- and 496-column backwards and the 256- and 1024-node
-forward segments and one more, two and three interior rows, chunk ends.  Every
-entry point against the oracle, node by node, in both boundary modes; the one-pass
-gradient bitwise bwd + bc on the rows both march."""
+62 output columns and one more, the 248- and 496-column backwards and the 256-node
+forward segments and one more, 1024-node forward segments with a ragged last one, two
+and three interior rows, chunk ends.  (tests/test_launch_rule.py holds the launches to
+that.)  Every entry point against the oracle, node by node, in both boundary modes; the
+one-pass gradient bitwise bwd + bc on the rows both march."""
 from __future__ import annotations
 
 import numpy as np
@@ -15,12 +16,26 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(3, 3), (4, 62), (5, 64), (3, 248), (9, 249), (40, 256), (33, 257), (130, 65), (12, 497),
           (21, 1025), (600, 6)]
+# grids whose forward takes the 1024-node segments
+WIDE = [(W.BURGERS_1DT, (200, 2047)), (W.HELMHOLTZ_2D, (500, 1010)), (W.BURGERS_1DT, (700, 2050)),
+        (W.NS_2D_STEADY, (500, 1950))]
 
 
 @pytest.mark.parametrize("bc_mode", [0, 1])
 @pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
 @pytest.mark.parametrize("op", [W.BURGERS_1DT, W.HELMHOLTZ_2D, W.NS_2D_STEADY])
 def test_row_edges(op, shape, bc_mode, oracle_mod):
+    _check_rows(op, shape, bc_mode, oracle_mod)
+
+
+@pytest.mark.parametrize("bc_mode", [0, 1])
+@pytest.mark.parametrize("op,shape", WIDE,
+                         ids=[f"{W.OP_NAMES[o]}-{'x'.join(map(str, s))}" for o, s in WIDE])
+def test_wide_segments(op, shape, bc_mode, oracle_mod):
+    _check_rows(op, shape, bc_mode, oracle_mod)
+
+
+def _check_rows(op, shape, bc_mode, oracle_mod):
     import torch  # noqa: PLC0415
     from paper_2607_18020_amd import binding as B  # noqa: PLC0415
     wl = W.normal_fields(op, shape, 46)

@@ -108,3 +108,65 @@ def test_checking_build_runs_other_tiles(rule, check_rule):
         assert len(a) == len(b) == 1
         tile = lambda x: (x.name, *x.args[:4 if x.name == "bwdt_kernel" else 2])  # noqa: E731
         assert tile(a[0]) != tile(b[0]), (what, a, b)
+
+
+def _march(ls):
+    (x,) = [x for x in ls if x.tiles and not x.name.startswith(("bc", "zero"))]
+    return x
+
+
+def test_edge_cases_of_the_3d_launches(rule):
+    """The grids of tests/test_gpu_launch_plans.py reach the edges that they are there for."""
+    from tests.test_gpu_launch_plans import CASES  # noqa: PLC0415
+    calls = ("fwd", "fwdR", "bwd", "vg", "vjp")
+    req = [(call, op, s, bc) for op, s in CASES for bc in (0, 1) for call in calls]
+    got = {q: _march(ls) for q, ls in zip(req, L.launches(rule, req))}
+    res = {(k, op, tx, ty): (a, b) for k, op, tx, ty, a, b in L.residency(rule)}
+    for call in calls:
+        space = {q: x for q, x in got.items() if q[0] == call and x.name != "bwdt_kernel"}
+        one = last_one = single = rounds = ragged = False
+        for (_, op, s, bc), x in space.items():
+            inner = 0 if bc or call in ("vg", "vjp") else 2
+            planes = (s[1] if len(s) == 4 else s[0]) - inner
+            chunks = -(-planes // x.chunk)
+            one |= x.chunk == 1 and chunks > 1
+            last_one |= x.chunk > 1 and planes % x.chunk == 1
+            single |= chunks == 1
+            tx, ty = int(x.args[0]), int(x.args[1])
+            per_cu = res[("fwd" if call == "fwdR" else call, op, tx, ty)][bc]
+            rounds |= chunks == 1 and x.tiles[0] * x.tiles[1] > 256 * per_cu
+            ragged |= s[-1] % tx == 1
+        assert (one or call == "vjp") and last_one and single and rounds and ragged, \
+            (call, one, last_one, single, rounds, ragged)
+    tiles = {(x.name, W.OP_NAMES[q[1]], *x.args[:2]) for q, x in got.items()}
+    for name, op, wide, narrow in [("fwd_kernel", W.NS_3D_BE, ("128", "4"), ("64", "8")),
+                                   ("fwd_kernel", W.HEAT_3D_BE, ("256", "4"), ("64", "8")),
+                                   ("bwd_kernel", W.NS_2DT, ("128", "8"), ("64", "8")),
+                                   ("vjp_kernel", W.HEAT_3D_BE, ("128", "8"), ("64", "8"))]:
+        for tile in (wide, narrow):
+            assert (name, W.OP_NAMES[op], *tile) in tiles, (name, op, tile)
+    blocks = {x.args[:3] for x in got.values() if x.name == "bwdt_kernel"}
+    assert blocks == {("4", "8", "32"), ("8", "6", "32"), ("8", "8", "32")}
+
+
+def test_edge_cases_of_the_2d_launches(rule):
+    """The grids of tests/test_gpu_rows.py: each segment width with a ragged last one."""
+    from tests.test_gpu_rows import SHAPES, WIDE  # noqa: PLC0415
+    ops = (W.BURGERS_1DT, W.HELMHOLTZ_2D, W.NS_2D_STEADY)
+    width = {"fwdq_kernel": lambda x: int(x.args[0]), "bwdq_kernel": lambda x: 62 * int(x.args[0])}
+    over = set()  # (operator, kernel, width) with one node in the last segment
+    req = [(call, op, s, bc) for op in ops for s in SHAPES for bc in (0, 1)
+           for call in ("fwd", "fwdR", "bwd", "vg", "vg_ws")]
+    for (call, op, s, bc), ls in zip(req, L.launches(rule, req)):
+        x = _march(ls)
+        w = width[x.name](x)
+        if s[1] % w == 1:
+            over.add((op, x.name, w))
+    for op in ops:
+        assert {(op, "fwdq_kernel", 256), (op, "bwdq_kernel", 248)} <= over
+        if op != W.NS_2D_STEADY:
+            assert (op, "bwdq_kernel", 496) in over
+    req = [(call, op, s, bc) for op, s in WIDE for bc in (0, 1) for call in ("fwd", "fwdR")]
+    for q, ls in zip(req, L.launches(rule, req)):
+        x = _march(ls)
+        assert x.args[0] == "1024" and q[2][1] % 1024 != 0, (q, x)
