@@ -200,10 +200,12 @@ def _loss_workspace(stream, dev) -> Optional[torch.Tensor]:
     """A zeroed loss workspace, allocated and zeroed on the stream whose calls use
     it; None while that stream is being captured (the zeroing would be part of
     the graph, and not done for calls outside it)."""
-    with torch.cuda.stream(stream):  # (None: the current stream)
-        if torch.cuda.is_current_stream_capturing():
-            return None
-        return torch.zeros(WORKSPACE_BYTES // 8, dtype=torch.float64, device=dev)
+    if stream is not None:
+        with torch.cuda.stream(stream):
+            return _loss_workspace(None, dev)
+    if torch.cuda.is_current_stream_capturing():
+        return None
+    return torch.zeros(WORKSPACE_BYTES // 8, dtype=torch.float64, device=dev)
 
 
 def fpde_residual_fwd(op: int, fields, consts, h, coeffs, *, residual_out=None,
