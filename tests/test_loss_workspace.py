@@ -109,9 +109,12 @@ def test_bound_losses(op, shape):
         a, b = fwd().item(), vg()[0].item()
         # float64 sums of at most 2^23 float32 squares in another order
         assert abs(a - ref) <= 1e-12 * ref and abs(b - ref) <= 1e-12 * ref, (k, a, b, ref)
-        if len(spec.fields) > 1:  # (fewer workgroups than slots: a fixed order)
+        if len(spec.fields) > 1:  # (no more workgroups than slots: a fixed order)
             first = first or (a, b)
-            assert (a, b) == first
+            assert a == first[0]
+            # (the checking build's narrow tiles make 7936 workgroups of the widest grid)
+            if os.environ.get("FPDE_TEST_LIBRARY") != "check" or shape[-1] < 1015808:
+                assert b == first[1]
 
 
 @pytest.mark.gpu
