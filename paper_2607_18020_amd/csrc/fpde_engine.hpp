@@ -1528,8 +1528,10 @@ __global__ __launch_bounds__(256) void bc_kernel(Ptrs P, Dims D, KCoef K, const 
 // (83 KB of fields and 54 KB of residuals at 8 x 8 x 32), so one workgroup runs
 // per CU, with one to four nodes per thread by what its registers hold (1024 threads
 // with two nodes each would spill; loads a phase earlier changed nothing).
-// A chunk of levels starts and ends with one level whose residuals are evaluated
-// at the block's own nodes only.
+// A chunk of levels starts and ends with one level whose residuals count at the block's
+// own nodes only, for the time part of the levels next to them: nothing is gathered
+// there.  (Its faces are evaluated all the same; the first level's leave the velocities
+// of t - 1 behind for the next one's.)
 template <int TZ, int TY, int TX, int NT>
 struct TBlock {
     static constexpr int NODES = TZ * TY * TX, NOWN = NODES / NT;

@@ -80,7 +80,7 @@ def test_bwd_writes_inner_levels_and_bc_the_end_levels():
 @pytest.mark.parametrize("bc_mode", [0, 1])
 def test_value_and_grad_is_bwd_plus_bc_bitwise(bc_mode):
     """The one-pass call forms every gradient node with the same instructions as
-    bwd + bc (level march, time march, end levels): bitwise equal; its loss is
+    bwd + bc (time march, end levels): bitwise equal; its loss is
     the forward's to float64 summation order."""
     import torch  # noqa: PLC0415
     from paper_2607_18020_amd import binding as B  # noqa: PLC0415
